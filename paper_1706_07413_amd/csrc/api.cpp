@@ -51,11 +51,12 @@ struct LaunchClass {
 // instances (classes `cls` of the context, all in configuration cfg).
 struct BigGroup {
     ClassCfg cfg;
-    int blocks = 0;
+    int blocks = 0;          // workgroups: the chunks of all its instances
     std::vector<int> cls;
     BigDesc* d_desc = nullptr;
-    double* xch = nullptr;              // exchange records [blocks][32]
-    unsigned long long* ctr = nullptr;  // [cls.size()][kBigCtrStride]: arrival counter, error flag
+    BigBlock* d_block = nullptr;
+    double* xch = nullptr;   // exchange records [blocks][kBigRecWords]
+    int32_t* err = nullptr;  // [cls.size()]: a wait of the instance's workgroups ran out
 };
 
 // Host-side tables of one grid size N.
@@ -176,8 +177,29 @@ ClassCfg choose_class(int N)
     return default_class(N);
 }
 
-// Chunk configuration for a grid too large for one workgroup: (4, 8), i.e.
-// 2048 points per workgroup, unless ADSCL_TUNE names another supported one.
+// Points of the last of the chunks of configuration c.
+int last_chunk(int N, ClassCfg c)
+{
+    const int C = 64 * c.W * c.P;
+    return (N - 1) - ((N - 1 + C - 1) / C - 1) * C;
+}
+
+// Whether chunks of configuration c suit a grid: not too many of them, the last one
+// large enough.
+bool chunks_fit(int N, ClassCfg c)
+{
+    const int C = 64 * c.W * c.P;
+    return (N - 1 + C - 1) / C <= kBigMaxChunks && last_chunk(N, c) >= kBigMinLast;
+}
+
+// Chunk configuration for a grid too large for one workgroup, unless ADSCL_TUNE
+// names another supported one: 768 points per workgroup, (4, 3), where the grid
+// allows it, else 1024, else 2048.  A stage is bound by latency, and the fewer
+// wavefronts share its barriers the shorter it is (N = 16385: 13.2 us per step
+// with 768 or 1024, 15.9 with 2048); four wavefronts with the helper's also let
+// three workgroups share a compute unit (64 fourth-order instances of 8193 points:
+// 18 us with 768, 28 with 1024, which fits once, 18 with 2048).  The choice hangs on N
+// alone, so that an instance is computed alike alone and in any batch.
 ClassCfg choose_big_class(int N)
 {
     if (const char* t = std::getenv("ADSCL_TUNE")) {
@@ -194,6 +216,8 @@ ClassCfg choose_big_class(int N)
             pos = end + 1;
         }
     }
+    for (const ClassCfg c : {ClassCfg{4, 3}, ClassCfg{4, 4}})
+        if (chunks_fit(N, c) && chunks_fit(N, ClassCfg{4, 8})) return c;
     return ClassCfg{4, 8};
 }
 
@@ -397,7 +421,8 @@ int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true)
         BigArgs x;
         x.desc = g.d_desc;
         x.xch = g.xch;
-        x.ctr = g.ctr;
+        x.err = g.err;
+        x.block = g.d_block;
         x.n_desc = (int32_t)g.cls.size();
         x.pad = 0;
         EvolveArgs a = base;
@@ -523,14 +548,11 @@ int run_call(adscl_ctx* c, int64_t max_steps, double t_end, int32_t snap_every, 
 int check_big(adscl_ctx* c)
 {
     for (const BigGroup& g : c->big_groups) {
-        std::vector<unsigned long long> ctr(kBigCtrStride * g.cls.size());
-        HIP_TRY(c, hipMemcpyAsync(ctr.data(), g.ctr, sizeof(unsigned long long) * ctr.size(), hipMemcpyDeviceToHost,
-                                  c->stream));
+        std::vector<int32_t> err(g.cls.size());
+        HIP_TRY(c, hipMemcpyAsync(err.data(), g.err, sizeof(int32_t) * err.size(), hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         for (size_t d = 0; d < g.cls.size(); ++d) {
-            int e = 0;
-            std::memcpy(&e, &ctr[d * kBigCtrStride + 1], sizeof(int));
-            if (e)
+            if (err[d])
                 return fail(c, ADSCL_EHIP, "instance " + std::to_string(c->classes[g.cls[d]].inst[0]) +
                                                ": a grid synchronisation of its workgroups timed out");
         }
@@ -949,8 +971,8 @@ int adscl_create(const adscl_config* cfg, void* hip_stream, adscl_ctx** out)
             const ClassCfg cfg = choose_big_class(N);
             const int C = 64 * cfg.W * cfg.P;
             const int G = (N - 1 + C - 1) / C;
-            const int rem = (N - 1) - (G - 1) * C;
-            if (G > kBigMaxChunks || rem < 8 || big_lds_bytes(cfg) > c->max_lds) {
+            const int rem = last_chunk(N, cfg);
+            if (!chunks_fit(N, cfg) || big_lds_bytes(cfg) > c->max_lds) {
                 c->err = "N=" + std::to_string(N) + ": no chunk configuration (chunks of " + std::to_string(C) +
                          " points leave " + std::to_string(rem) + " in the last)";
                 return bail(ADSCL_EUNSUPPORTED);
@@ -1119,9 +1141,14 @@ int adscl_create(const adscl_config* cfg, void* hip_stream, adscl_ctx** out)
         }
         TRY_C(hipMalloc((void**)&g.d_desc, sizeof(BigDesc) * desc.size()));
         TRY_C(hipMemcpy(g.d_desc, desc.data(), sizeof(BigDesc) * desc.size(), hipMemcpyHostToDevice));
-        TRY_C(hipMalloc((void**)&g.xch, sizeof(double) * 32 * (size_t)g.blocks));
-        TRY_C(hipMalloc((void**)&g.ctr, sizeof(unsigned long long) * kBigCtrStride * desc.size()));
-        TRY_C(hipMemset(g.ctr, 0, sizeof(unsigned long long) * kBigCtrStride * desc.size()));
+        std::vector<BigBlock> blk;
+        for (int d = 0; d < (int)desc.size(); ++d)
+            for (int ch = 0; ch < desc[d].chunks; ++ch) blk.push_back(BigBlock{d, ch});
+        TRY_C(hipMalloc((void**)&g.d_block, sizeof(BigBlock) * blk.size()));
+        TRY_C(hipMemcpy(g.d_block, blk.data(), sizeof(BigBlock) * blk.size(), hipMemcpyHostToDevice));
+        TRY_C(hipMalloc((void**)&g.xch, sizeof(double) * kBigRecWords * (size_t)g.blocks));
+        TRY_C(hipMalloc((void**)&g.err, sizeof(int32_t) * desc.size()));
+        TRY_C(hipMemset(g.err, 0, sizeof(int32_t) * desc.size()));
     }
 
     std::vector<const double*> tabp(c->n_inst), ep(c->n_inst), wpp(c->n_inst), wfp(c->n_inst);
@@ -1161,8 +1188,9 @@ void adscl_destroy(adscl_ctx* c)
     if (c->stream) (void)hipStreamSynchronize(c->stream);
     for (BigGroup& g : c->big_groups) {
         if (g.d_desc) (void)hipFree(g.d_desc);
+        if (g.d_block) (void)hipFree(g.d_block);
         if (g.xch) (void)hipFree(g.xch);
-        if (g.ctr) (void)hipFree(g.ctr);
+        if (g.err) (void)hipFree(g.err);
     }
     for (LaunchClass& lc : c->classes) {
         if (lc.d_order) (void)hipFree(lc.d_order);

@@ -94,21 +94,26 @@ hipError_t prepare_evolve_scheme(ClassCfg c, int rk, bool eva, size_t max_lds);
 hipError_t launch_evolve_scheme(ClassCfg c, int rk, bool eva, bool full, int n_blocks, const EvolveArgs& a,
                                 hipStream_t s);
 
-// One large instance of a (merged) launch of the multi-workgroup kernel: its
-// workgroups are [first, first + chunks) of the launch.
+// One large instance of a (merged) launch of the multi-workgroup kernel.
 struct BigDesc {
     int32_t inst;             // instance index
     int32_t chunks;           // G
-    int32_t first;            // its first workgroup in the launch, and its first exchange record
+    int32_t first;            // its first exchange record
     int32_t pad;
+};
+// One workgroup of that launch: chunk `chunk` of instance desc[desc].
+struct BigBlock {
+    int32_t desc;
+    int32_t chunk;
 };
 // The pointers sit in the kernel arguments (not in the table) so that the
 // compiler knows they address global memory and emits global, not flat,
-// loads and atomics for the exchange records and counters.
+// loads and atomics for the exchange records and flags.
 struct BigArgs {
     const BigDesc* desc;      // device [n_desc]
-    double* xch;              // exchange records [blocks][32], in launch order
-    unsigned long long* ctr;  // per instance: arrival counter, then the error flag (int) [n_desc][kBigCtrStride]
+    const BigBlock* block;    // device [workgroups of the launch]
+    double* xch;              // exchange records [workgroups of the launch][kBigRecWords]
+    int32_t* err;             // per instance: set when a wait for another workgroup ran out [n_desc]
     int32_t n_desc;
     int32_t pad;
 };
@@ -126,9 +131,12 @@ hipError_t launch_evolve_big(ClassCfg c, int rk, bool eva, int blocks, const Evo
 // At most 64 chunks: the kernel scans the chunks' totals and gathers their
 // collapse bits with one wavefront lane per chunk.
 constexpr int kBigMaxChunks = 64;
-// 64-bit words between two instances' barrier counters: one 256-byte block
-// each, so that the instances of a launch do not poll and count on one line.
-constexpr int kBigCtrStride = 32;
+// The last chunk has at least this many points: its neighbour's halo, and the end's
+// stencils, lie inside it.
+constexpr int kBigMinLast = 8;
+// 64-bit words of one chunk's exchange record: four slots of three 128-byte
+// lines, and a line for the check bits.
+constexpr int kBigRecWords = 208;
 
 // Initial data: Pi = (2 eps/pi) exp(-4 tan^2 x/(pi^2 sigma^2)), Phi = 0 (pins applied).
 hipError_t launch_init_gaussian(int n_inst, const InstConst* ic, const double* eps, const double* sigma,

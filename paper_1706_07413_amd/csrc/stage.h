@@ -134,6 +134,24 @@ __device__ __forceinline__ double wave_incl_suffix(double v)
     return v + right;
 }
 
+// Sums of the wavefront totals r[0..W): over the wavefronts before this one
+// (`before`) and over all (`all`).  Lanes v < W hold r[v], a DPP prefix
+// runs over them (W <= 16: within the first row of 16 lanes), and two
+// wavefront-uniform lane reads broadcast the results, instead of every lane
+// adding all W totals under a mask.
+template <int W>
+__device__ __forceinline__ void wave_totals(const double* r, int lane, int wv, double& before, double& all)
+{
+    double x = (lane < W) ? r[lane < W ? lane : 0] : 0.0;
+    if constexpr (W > 1) x += dpp_d<0x111, 0xf>(x);  // row_shr:1
+    if constexpr (W > 2) x += dpp_d<0x112, 0xf>(x);  // row_shr:2
+    if constexpr (W > 4) x += dpp_d<0x114, 0xf>(x);  // row_shr:4
+    if constexpr (W > 8) x += dpp_d<0x118, 0xf>(x);  // row_shr:8
+    all = readlane_d(x, W - 1);
+    const int w = __builtin_amdgcn_readfirstlane(wv);
+    before = (w > 0) ? readlane_d(x, w > 0 ? w - 1 : 0) : 0.0;
+}
+
 // A lane-interleaved global array of doubles, [field][P][64 W]: entry (f, k) of
 // lane l at ((f P + k) 64 W + l).  Held as a uniform base and the lane's byte
 // offset, the latter opaque to the compiler, so that each access is a scalar
@@ -190,17 +208,6 @@ __device__ __forceinline__ StageRec<P, NL> stage_rec(ADSCL_GLOBAL double* base, 
     asm volatile("" : "+v"(o));
     return StageRec<P, NL>{(ADSCL_GLOBAL char*)base, o};
 }
-
-// LDS of the row layout used by the chunked large-grid kernel.
-template <int P, int W>
-struct StageLayout {
-    static constexpr int NL = 64 * W;      // lanes per instance
-    static constexpr int RS = NL + 2;      // LDS row: column 0 = lane -1, NL+1 = lane NL
-    static constexpr int SLOTS = P * RS;
-    // U and F: 2 x SLOTS pairs; sigma edges: 2 NL; reductions: 4 W + 8; with
-    // P >= 8, a separate region for the p edges (2 NL)
-    static constexpr size_t lds_doubles = (size_t)4 * SLOTS + 2 * NL + 4 * W + 8 + (P >= 8 ? 2 * NL : 0);
-};
 
 template <int P, int W, bool FULL, bool FWD = false>
 struct Stage {
@@ -423,21 +430,9 @@ struct Stage {
         }
     }
 
-    // Sums of the wavefront totals r[0..W): over the wavefronts before this one
-    // (`before`) and over all (`all`).  Lanes v < W hold r[v], a DPP prefix
-    // runs over them (W <= 16: within the first row of 16 lanes), and two
-    // wavefront-uniform lane reads broadcast the results, instead of every lane
-    // adding all W totals under a mask.
     __device__ __forceinline__ void wave_totals(const double* r, double& before, double& all) const
     {
-        double x = (lane < W) ? r[lane < W ? lane : 0] : 0.0;
-        if constexpr (W > 1) x += dpp_d<0x111, 0xf>(x);  // row_shr:1
-        if constexpr (W > 2) x += dpp_d<0x112, 0xf>(x);  // row_shr:2
-        if constexpr (W > 4) x += dpp_d<0x114, 0xf>(x);  // row_shr:4
-        if constexpr (W > 8) x += dpp_d<0x118, 0xf>(x);  // row_shr:8
-        all = readlane_d(x, W - 1);
-        const int w = __builtin_amdgcn_readfirstlane(wv);
-        before = (w > 0) ? readlane_d(x, w > 0 ? w - 1 : 0) : 0.0;
+        adscl::wave_totals<W>(r, lane, wv, before, all);
     }
 
     // Constraint solve of the published state given q = Phi^2 + Pi^2 of the own

@@ -204,3 +204,50 @@ def test_several_large_instances_side_by_side():
         one.close()
         for f in FIELDS:
             assert np.array_equal(b.split(g[f])[i], g1[f]), (i, f)
+
+
+# Where chunks of 768, 1024 and 2048 points can go wrong: a last chunk of exactly 8
+# points (6153: 768; 5129 with 1024, 4105 with 2048), the end in the first, second,
+# third and last point of a lane and at a wavefront's end, one chunk more than 768-point ones
+# allow (65537) beside the most (49153), and 4611, whose last chunk would be too
+# small with 768 points.
+CHUNKED = [(6153, ""), (5129, "4x4"), (4105, "4x8"), (6915, ""), (6917, ""), (6919, ""), (6913, ""), (6721, ""),
+           (49153, ""), (4611, "")]
+
+
+@pytest.mark.parametrize("N,tune", CHUNKED)
+def test_chunk_ends(monkeypatch, N, tune):
+    if tune:
+        monkeypatch.setenv("ADSCL_TUNE", "%d:%s" % (N, tune))
+    c = np.array([[1.0, 0.6, -0.2]])
+    print("chunk ends", N, tune, flush=True)
+    n = 40
+    for rk, K in ((4, 0), (3, 0), (3, 5), (2, 3)) if N < 20000 else ((4, 0),):
+        b = adscl.Batch([N], n_modes=3, rk_order=rk, a_reint=K)
+        b.init_modes(np.array([0.3]), c)
+        b.step(n, 1e9)
+        assert b.status()["steps"][0] == n
+        g = gpu_state(b)
+        b.close()
+        Phi, Pi = O.init_modes(N, 0.3, c[0])
+        ref = O.evolve_scheme(Phi, Pi, n, rk=rk, a_reint=K)
+        for f in FIELDS:
+            assert_close(g[f], ref[f], "N=%d rk %d K %d %s" % (N, rk, K, f))
+
+
+def test_large_instance_with_nan_data_stops_at_the_start():
+    """Data holding the signalling-NaN pattern that marks an empty exchange word
+    (at a chunk's first point) end as non-finite at step 0, not as a wait."""
+    N = 8193
+    Phi, Pi = np.zeros(N), np.cos(np.linspace(0.0, np.pi / 2, N)) ** 3
+    Phi.view(np.uint64)[768] = 0x7FF4C0DE5EEDFACE
+    b = adscl.Batch([N])
+    b.init(Phi, Pi)
+    assert b.status()["state"][0] == adscl.NONFINITE
+    b.step(4, 1e9)
+    st = b.status()
+    assert st["state"][0] == adscl.NONFINITE and st["steps"][0] == 0
+    f = adscl.Batch([N], flags=adscl.FROZEN_METRIC)
+    f.init(Phi, Pi)
+    f.step(4, 1e9)
+    assert f.status()["state"][0] == adscl.NONFINITE and f.status()["steps"][0] == 0
