@@ -63,6 +63,7 @@ struct BigGroup {
 struct NTables {
     ClassCfg cfg;
     double* d_tab = nullptr;     // lane-interleaved sc, t2, ct2 for cfg
+    double* d_nat = nullptr;     // tables in grid order (kNat*)
     double* d_emode = nullptr;   // e_j(x_i), [J][N]
     double* d_wPi = nullptr;     // h tan^2 x e_j, [J][N]
     double* d_wPhi = nullptr;    // h tan^2 x e_j'/omega_j, [J][N]
@@ -89,6 +90,7 @@ struct adscl_ctx {
     InstConst* d_ic = nullptr;
     std::vector<InstConst> h_ic;
     const double** d_tab = nullptr;
+    const double** d_nat = nullptr;
     const double** d_emode = nullptr;
     const double** d_wPi = nullptr;
     const double** d_wPhi = nullptr;
@@ -221,30 +223,27 @@ ClassCfg choose_big_class(int N)
     return ClassCfg{4, 8};
 }
 
-// sin, cos in long double for the tables (the kernel reads FP64 values).
-// `chunks` > 1: one [3][P][64 W] block per chunk of 64 W P points.
-void host_tables(int N, ClassCfg cfg, std::vector<double>& tab, int chunks = 1)
+// Coefficient tables from sin, cos in long double (the kernels read FP64 values):
+// `tab` lane-interleaved for cfg (`chunks` > 1: one [3][P][64 W] block per chunk of
+// 64 W P points), `nat` in grid order.
+void host_tables(int N, ClassCfg cfg, std::vector<double>& tab, std::vector<double>& nat, int chunks = 1)
 {
     const int NL = 64 * cfg.W, P = cfg.P;
     tab.assign(table_len(cfg) * chunks, 0.0);
+    nat.assign((size_t)kNatTables * N, 0.0);
     const long double h = (3.14159265358979323846264338327950288L / 2.0L) / (long double)(N - 1);
-    for (int ch = 0; ch < chunks; ++ch)
-    for (int lane = 0; lane < NL; ++lane) {
-        for (int k = 0; k < P; ++k) {
-            const int i = ch * NL * P + lane * P + k;
-            double sc = 0.0, t2 = 0.0, ct2 = 0.0;
-            if (i >= 1 && i <= N - 2) {
-                const long double x = h * (long double)i;
-                const long double s = sinl(x), c = cosl(x);
-                sc = (double)(s * c);
-                t2 = (double)((s * s) / (c * c));
-                ct2 = (double)((c * c) / (s * s));
-            }
-            const size_t base = (size_t)ch * table_len(cfg);
-            tab[base + (size_t)(0 * P + k) * NL + lane] = sc;
-            tab[base + (size_t)(1 * P + k) * NL + lane] = t2;
-            tab[base + (size_t)(2 * P + k) * NL + lane] = ct2;
-        }
+    for (int i = 1; i <= N - 2; ++i) {
+        const long double x = h * (long double)i;
+        const long double s = sinl(x), c = cosl(x);
+        const double v[3] = {(double)(s * c), (double)((s * s) / (c * c)), (double)((c * c) / (s * s))};
+        const int ch = i / (NL * P), lane = i % (NL * P) / P, k = i % P;
+        for (int t = 0; t < 3; ++t)
+            tab[(size_t)ch * table_len(cfg) + (size_t)(t * P + k) * NL + lane] = v[t];
+        nat[(size_t)kNatSC * N + i] = v[0];
+        nat[(size_t)kNatT2 * N + i] = v[1];
+        nat[(size_t)kNatC3S * N + i] = (double)(c * c * c / s);
+        nat[(size_t)kNatCT2 * N + i] = v[2];
+        nat[(size_t)kNatRA * N + i] = (double)((1.0L + 2.0L * s * s) / (s * c));
     }
 }
 
@@ -469,7 +468,7 @@ int run_evolve(adscl_ctx* c, int32_t snap_every) { return run_evolve(c, evolve_a
 
 int run_finalize(adscl_ctx* c, bool final, int32_t snap_every, int32_t n_slots, double* snaps)
 {
-    HIP_TRY(c, launch_finalize(c->n_inst, c->d_ic, c->d_status, c->state5, c->total, c->gauge,
+    HIP_TRY(c, launch_finalize(c->n_inst, c->max_N, c->d_ic, c->d_status, c->d_nat, c->state5, c->total, c->gauge,
                                (c->flags & ADSCL_FROZEN_METRIC) ? 1 : 0, c->thr, final, snap_every, n_slots,
                                snaps, c->stream, c->a_reint));
     return ADSCL_OK;
@@ -981,10 +980,12 @@ int adscl_create(const adscl_config* cfg, void* hip_stream, adscl_ctx** out)
                 NTables t;
                 t.cfg = cfg;
                 TRY_C(prepare_evolve_big(cfg, c->rk, c->a_reint > 0, c->max_lds));
-                std::vector<double> tab, e, wpi, wphi;
-                host_tables(N, cfg, tab, G);
+                std::vector<double> tab, nat, e, wpi, wphi;
+                host_tables(N, cfg, tab, nat, G);
                 TRY_C(hipMalloc((void**)&t.d_tab, tab.size() * sizeof(double)));
                 TRY_C(hipMemcpy(t.d_tab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice));
+                TRY_C(hipMalloc((void**)&t.d_nat, nat.size() * sizeof(double)));
+                TRY_C(hipMemcpy(t.d_nat, nat.data(), nat.size() * sizeof(double), hipMemcpyHostToDevice));
                 if (c->n_modes > 0) {
                     host_modes(N, c->n_modes, e, wpi, wphi);
                     const size_t bytes = e.size() * sizeof(double);
@@ -1020,10 +1021,12 @@ int adscl_create(const adscl_config* cfg, void* hip_stream, adscl_ctx** out)
             if (scheme(c)) TRY_C(prepare_evolve_scheme(t.cfg, c->rk, c->a_reint > 0, c->max_lds));
             else TRY_C(prepare_evolve(t.cfg, c->max_lds));
             TRY_C(prepare_adjoint(t.cfg, c->max_lds));
-            std::vector<double> tab, e, wpi, wphi;
-            host_tables(N, t.cfg, tab);
+            std::vector<double> tab, nat, e, wpi, wphi;
+            host_tables(N, t.cfg, tab, nat);
             TRY_C(hipMalloc((void**)&t.d_tab, tab.size() * sizeof(double)));
             TRY_C(hipMemcpy(t.d_tab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice));
+            TRY_C(hipMalloc((void**)&t.d_nat, nat.size() * sizeof(double)));
+            TRY_C(hipMemcpy(t.d_nat, nat.data(), nat.size() * sizeof(double), hipMemcpyHostToDevice));
             if (c->n_modes > 0) {
                 host_modes(N, c->n_modes, e, wpi, wphi);
                 const size_t bytes = e.size() * sizeof(double);
@@ -1151,16 +1154,19 @@ int adscl_create(const adscl_config* cfg, void* hip_stream, adscl_ctx** out)
         TRY_C(hipMemset(g.err, 0, sizeof(int32_t) * desc.size()));
     }
 
-    std::vector<const double*> tabp(c->n_inst), ep(c->n_inst), wpp(c->n_inst), wfp(c->n_inst);
+    std::vector<const double*> tabp(c->n_inst), natp(c->n_inst), ep(c->n_inst), wpp(c->n_inst), wfp(c->n_inst);
     for (int b = 0; b < c->n_inst; ++b) {
         const NTables& t = c->tables[c->N[b]];
         tabp[b] = t.d_tab;
+        natp[b] = t.d_nat;
         ep[b] = t.d_emode;
         wpp[b] = t.d_wPi;
         wfp[b] = t.d_wPhi;
     }
     const size_t pb = sizeof(double*) * c->n_inst;
     TRY_C(hipMalloc((void**)&c->d_tab, pb));
+    TRY_C(hipMalloc((void**)&c->d_nat, pb));
+    TRY_C(hipMemcpy(c->d_nat, natp.data(), pb, hipMemcpyHostToDevice));
     TRY_C(hipMalloc((void**)&c->d_emode, pb));
     TRY_C(hipMalloc((void**)&c->d_wPi, pb));
     TRY_C(hipMalloc((void**)&c->d_wPhi, pb));
@@ -1202,11 +1208,13 @@ void adscl_destroy(adscl_ctx* c)
     }
     for (auto& kv : c->tables) {
         if (kv.second.d_tab) (void)hipFree(kv.second.d_tab);
+        if (kv.second.d_nat) (void)hipFree(kv.second.d_nat);
         if (kv.second.d_emode) (void)hipFree(kv.second.d_emode);
         if (kv.second.d_wPi) (void)hipFree(kv.second.d_wPi);
         if (kv.second.d_wPhi) (void)hipFree(kv.second.d_wPhi);
     }
     if (c->d_tab) (void)hipFree((void*)c->d_tab);
+    if (c->d_nat) (void)hipFree((void*)c->d_nat);
     if (c->d_emode) (void)hipFree((void*)c->d_emode);
     if (c->d_wPi) (void)hipFree((void*)c->d_wPi);
     if (c->d_wPhi) (void)hipFree((void*)c->d_wPhi);
@@ -1333,11 +1341,8 @@ int adscl_status(adscl_ctx* c, double* t, int64_t* steps, int32_t* state, double
 static int constraints_call(adscl_ctx* c, double* scr, double* out, int mem)
 {
     double* dst = mem == ADSCL_MEM_DEVICE ? out : scr + 2 * c->total;
-    const double* s = c->state5;
-    HIP_TRY(c, launch_diagnostics(c->n_inst, c->d_ic, s, s + c->total, s + 2 * c->total, s + 3 * c->total,
-                                  s + 4 * c->total, dst, c->stream));
-    const int frozen = (c->flags & ADSCL_FROZEN_METRIC) ? 1 : 0;
-    HIP_TRY(c, launch_adot_residual(c->n_inst, c->d_ic, s, c->total, frozen, c->ko, scr, dst, c->stream));
+    HIP_TRY(c, launch_diagnostics(c->n_inst, c->d_ic, c->d_nat, c->state5, c->total,
+                                  (c->flags & ADSCL_FROZEN_METRIC) ? 1 : 0, c->ko, scr, dst, c->stream));
     if (mem == ADSCL_MEM_HOST) {
         HIP_TRY(c, hipMemcpyAsync(out, dst, sizeof(double) * 5 * c->n_inst, hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));

@@ -2,7 +2,9 @@
 // AdS4 scalar-collapse library (Liebling & Khanna, arXiv:1706.07413, Sec. II).
 #include <math.h>
 
-#include "internal.h"
+#include <algorithm>
+
+#include "stage.h"
 
 namespace adscl {
 namespace {
@@ -80,30 +82,31 @@ __global__ void set_targets_kernel(int n_inst, const InstConst* ic, InstStatus* 
     st[b] = o;
 }
 
-// Block-wide exclusive prefix sum of one value per thread (256 threads).
-__device__ double block_excl_scan(double v, double* sh, double& total)
+// Block-wide exclusive prefix sum of one value per thread (up to 1024 threads) and
+// its total; contains one barrier.  `sh`: 16 doubles that no wavefront still reads
+// from an earlier call (callers alternate between two).
+__device__ __forceinline__ double block_scan(double v, double* sh, double& total)
 {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    double x = v;
-    for (int d = 1; d < 64; d <<= 1) {
-        const double t = __shfl_up(x, d, 64);
-        if (lane >= d) x += t;
-    }
-    __syncthreads();
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const double x = wave_incl_scan(v);
     if (lane == 63) sh[wv] = x;
     __syncthreads();
-    double carry = 0.0;
-    total = 0.0;
-    for (int w = 0; w < 4; ++w) {
-        if (w < wv) carry += sh[w];
-        total += sh[w];
-    }
-    return carry + x - v;
+    double w = (lane < nw) ? sh[lane < nw ? lane : 0] : 0.0;
+    w += dpp_d<0x111, 0xf>(w);  // at most 16 wavefronts: a prefix over one row of lanes
+    w += dpp_d<0x112, 0xf>(w);
+    w += dpp_d<0x114, 0xf>(w);
+    w += dpp_d<0x118, 0xf>(w);
+    total = readlane_d(w, 15);
+    const int u = __builtin_amdgcn_readfirstlane(wv);
+    // the lanes before: the left lane's sum, not this one's less v, which would lose
+    // the small sums near x = 0 next to a far larger v
+    return (u > 0 ? readlane_d(w, u > 0 ? u - 1 : 0) : 0.0) + dpp_d<0x138, 0xf>(x);
 }
 
 struct FinArgs {
     const InstConst* ic;
     InstStatus* st;
+    const double* const* nat;  // tables in grid order per instance (kNat*)
     double* state5;
     int64_t total;
     double a_collapse;
@@ -116,163 +119,169 @@ struct FinArgs {
     int32_t a_reint;  // > 0: A is evolved; the state's A is kept unless steps % a_reint == 0
 };
 
-// Constraint solve of the packed state of one instance per 256-thread block
-// (Sec. II, Eqs. (5)-(6), the same discretisation as the evolution kernel:
-// 4-point cell rule in prefix-sum form, m = (1 - A) sin x / cos^3 x), written
-// out as (Phi, Pi, A, delta, m); then min A, the mass m(pi/2) and, at the end
-// of a call, the collapse / non-finite test of the final state.  With A evolved
-// (a_reint > 0) the state's A is kept (and tested) except at steps that are a
-// multiple of a_reint, where the solve's A replaces it as the evolution would.
-__global__ void __launch_bounds__(256) finalize_kernel(FinArgs f)
+constexpr int kFinK = 4;  // consecutive points per thread
+
+// Constraint solve of the packed state of one instance per block (Sec. II,
+// Eqs. (5)-(6), the same discretisation as the evolution kernel: 4-point cell rule
+// in prefix-sum form, m = (1 - A) sin x / cos^3 x), written out as (Phi, Pi, A,
+// delta, m); then min A, the mass m(pi/2) and, at the end of a call, the collapse /
+// non-finite test of the final state.  With A evolved (a_reint > 0) the state's A
+// is kept (and tested) except at steps that are a multiple of a_reint, where the
+// solve's A replaces it as the evolution would.
+//
+// The interior points 1 .. N-2 go in tiles of four consecutive ones per thread; the
+// running sums carry over the tiles.  The first pass takes the total of p (the
+// boundary gauge's shift enters every exponential), the second the two prefix sums
+// side by side.  A thread forms p and sigma at its neighbours' adjacent points
+// itself (two more exponentials for its four) instead of exchanging them, so that
+// two scans are a tile's only barriers; the coefficients come from tables in grid order.
+// Bound by the latency of those scans and of the loads: one instance of 513, 1025,
+// 16385 and 32769 points 9.1, 9.9, 54 and 92 us, against 18, 28, 342 and 608 with
+// 256 threads, a run of N/256 points each, and sin, cos, tan and three exponentials
+// per point; 64 instances of 4097 points 19 against 90, a batch of 1024 (1025 to
+// 4097 points) 62 against 457.
+__global__ void __launch_bounds__(1024) finalize_kernel(FinArgs f)
 {
-    __shared__ double sh[16];
-    __shared__ int ish[4];
+    __shared__ double sh[3][16];
+    __shared__ int ish[16];
     const int b = blockIdx.x;
     const InstStatus st = f.st[b];
     const InstConst c = f.ic[b];
     const bool snap = f.snaps && f.snap_every > 0 && (st.steps % f.snap_every) == 0 &&
                       (st.steps / f.snap_every) < f.n_slots;
     if (!snap && !f.final_) return;
-    const int N = c.N;
-    const double h = c.h;
-    const double* Phi = f.state5 + c.off;
-    const double* Pi = f.state5 + f.total + c.off;
-    double* dst[2] = {f.final_ ? f.state5 : nullptr,
-                      snap ? f.snaps + (size_t)(st.steps / f.snap_every) * 5 * (size_t)f.total : nullptr};
-    // scratch for delta~ before the gauge shift: the delta row of the first target
-    double* dscr = (dst[0] ? dst[0] : dst[1]) + 3 * f.total + c.off;
-
-    const int tid = threadIdx.x;
-    const int C = (N + 255) / 256;
-    const int i0 = tid * C;
-    const int i1 = min(N, i0 + C);
-    auto q_at = [&](int i) -> double { return Phi[i] * Phi[i] + Pi[i] * Pi[i]; };
-    auto sc_at = [&](int i) -> double {
-        const double x = (double)i * h;
-        return sin(x) * cos(x);
+    constexpr int K = kFinK;
+    const int N = c.N, tid = threadIdx.x, tile = blockDim.x * K;
+    const double h24 = c.h24;
+    const ADSCL_GLOBAL double* const Phi = gmem(f.state5 + c.off);
+    const ADSCL_GLOBAL double* const Pi = gmem(f.state5 + f.total + c.off);
+    const ADSCL_GLOBAL double* const Arow = gmem(f.state5 + 2 * f.total + c.off);
+    const ADSCL_GLOBAL double* const nat = gmem(f.nat[b]);
+    double* const dst[2] = {f.final_ ? f.state5 + c.off : nullptr,
+                            snap ? f.snaps + (size_t)(st.steps / f.snap_every) * 5 * (size_t)f.total + c.off : nullptr};
+    auto put = [&](int row, int i, double v) {
+        if (dst[0]) dst[0][row * f.total + i] = v;
+        if (dst[1]) dst[1][row * f.total + i] = v;
     };
-    auto t2_at = [&](int i) -> double {
-        const double t = tan((double)i * h);
-        return t * t;
-    };
-    // p = sin x cos x q: 0 at both ends, odd ghosts about both ends
-    auto p_at = [&](int i) -> double {
-        double sgn = 1.0;
-        if (i < 0) { i = -i; sgn = -1.0; }
-        if (i > N - 1) { i = 2 * (N - 1) - i; sgn = -sgn; }
-        if (i == 0 || i == N - 1) return 0.0;
-        return sgn * sc_at(i) * q_at(i);
-    };
-
-    double dN = 0.0, tot2 = 0.0, shift = 0.0;
-    if (!f.frozen) {
-        double ps = 0.0;
-        for (int i = i0; i < i1; ++i) ps += p_at(i);
-        double tot;
-        const double carry = block_excl_scan(ps, sh, tot);
-        const double p1 = p_at(1);
-        double R = carry;
-        for (int i = i0; i < i1; ++i) {
-            const double pi_ = p_at(i);
-            R += pi_;
-            dscr[i] = -(h / 24.0) * (24.0 * R - 12.0 * pi_ + p_at(i - 1) - p_at(i + 1) + 2.0 * p1);
-        }
-        dN = -(h / 24.0) * (24.0 * tot + 2.0 * p_at(N - 2) + 2.0 * p1);
-        shift = (f.gauge == 0) ? dN : 0.0;
-        __syncthreads();
-    }
-    // sigma = tan^2 x q e^{-delta}: 0 at both ends, even ghosts
-    auto sig_at = [&](int i) -> double {
-        if (i < 0) i = -i;
-        if (i > N - 1) i = 2 * (N - 1) - i;
-        if (i == 0 || i == N - 1) return 0.0;
-        return t2_at(i) * q_at(i) * exp(-(dscr[i] - shift));
-    };
-    double mn = 1.0, chk = 0.0;
-    int col = 0;
     const bool keepA = f.a_reint > 0 && (st.steps % f.a_reint) != 0;
-    const double* Arow = f.state5 + 2 * f.total + c.off;
+    double mn = 1.0, chk = 0.0, dN = 0.0, tot2 = 0.0;
+    int col = 0;
+
     if (!f.frozen) {
-        double ss = 0.0;
-        for (int i = i0; i < i1; ++i) ss += sig_at(i);
-        double carry2 = block_excl_scan(ss, sh + 4, tot2);
-        double R2 = carry2;
-        for (int i = i0; i < i1; ++i) {
-            const double si = sig_at(i);
-            R2 += si;
-            const double S = (h / 24.0) * (24.0 * R2 - 12.0 * si + sig_at(i - 1) - sig_at(i + 1));
-            const double dl = dscr[i] - shift;
-            const double E = exp(-dl);
-            const double m = S / E;
-            double A = 1.0;
-            if (keepA) {
-                A = Arow[i];
-                if (A < f.a_collapse) col = 1;
-            } else if (i >= 1 && i <= N - 2) {
-                const double x = (double)i * h;
-                const double s = sin(x), co = cos(x);
-                const double c3s = co * co * co / s;
-                A = 1.0 - c3s * m;
-                if (E - c3s * S < f.a_collapse * E) col = 1;
+        // q and p = sin x cos x q (0 at both ends and past them)
+        auto q_at = [&](int i) -> double { return Phi[i] * Phi[i] + Pi[i] * Pi[i]; };
+        double tot = 0.0;
+        {
+            double s = 0.0;
+            for (int i = 1 + tid; i <= N - 2; i += blockDim.x) s += nat[kNatSC * N + i] * q_at(i);
+            block_scan(s, sh[2], tot);
+        }
+        const double p1 = nat[kNatSC * N + 1] * q_at(1), pN2 = nat[kNatSC * N + N - 2] * q_at(N - 2);
+        dN = -h24 * (24.0 * tot + 2.0 * pN2 + 2.0 * p1);
+        const double shift = (f.gauge == 0) ? dN : 0.0;
+        double carry = 0.0, carry2 = 0.0;  // sums over the tiles before
+        for (int t0 = 1; t0 <= N - 2; t0 += tile) {
+            const int i0 = t0 + tid * K;
+            // p and q at i0 - 2 .. i0 + K + 1, index i - i0 + 2
+            double p[K + 4], q[K + 4], ps = 0.0;
+#pragma unroll
+            for (int k = 0; k < K + 4; ++k) {
+                const int i = i0 - 2 + k;
+                const bool in = i >= 1 && i <= N - 2;
+                q[k] = in ? q_at(i) : 0.0;
+                p[k] = in ? nat[kNatSC * N + i] * q[k] : 0.0;
+                if (k >= 2 && k < K + 2) ps += p[k];
             }
+            double tt;
+            const double R0 = carry + block_scan(ps, sh[0], tt);  // sum of p before i0
+            carry += tt;
+            // delta~, e^-delta and sigma = tan^2 x q e^-delta at i0 - 1 .. i0 + K, index i - i0 + 1
+            double dl[K + 2], E[K + 2], sg[K + 2], ss = 0.0, R = R0 - p[1];
+#pragma unroll
+            for (int k = 0; k < K + 2; ++k) {
+                const int i = i0 - 1 + k;
+                const bool in = i >= 1 && i <= N - 2;
+                R += p[k + 1];
+                dl[k] = -h24 * (24.0 * R - 12.0 * p[k + 1] + p[k] - p[k + 2] + 2.0 * p1) - shift;
+                E[k] = exp(-dl[k]);
+                sg[k] = in ? nat[kNatT2 * N + i] * q[k + 1] * E[k] : 0.0;
+                if (k >= 1 && k < K + 1) ss += sg[k];
+            }
+            double R2 = carry2 + block_scan(ss, sh[1], tt);
+            carry2 += tt;
+#pragma unroll
+            for (int k = 1; k < K + 1; ++k) {
+                const int i = i0 - 1 + k;
+                if (i > N - 2) break;
+                R2 += sg[k];
+                const double S = h24 * (24.0 * R2 - 12.0 * sg[k] + sg[k - 1] - sg[k + 1]);
+                const double m = S / E[k], c3s = nat[kNatC3S * N + i];
+                double A;
+                if (keepA) {
+                    A = Arow[i];
+                    if (A < f.a_collapse) col = 1;
+                } else {
+                    A = 1.0 - c3s * m;
+                    if (E[k] - c3s * S < f.a_collapse * E[k]) col = 1;
+                }
+                mn = fmin(mn, A);
+                chk = fma(q[k + 1], 0.0, chk);
+                chk = fma(A, 0.0, chk);
+                chk = fma(dl[k], 0.0, chk);
+                put(2, i, A);
+                put(3, i, dl[k]);
+                put(4, i, m);
+            }
+        }
+        tot2 = carry2;
+        if (tid < 2) {  // the ends: A = 1, delta~ = 0 at x = 0 and dN at pi/2, S = 0 and h sum sigma
+            const int i = tid == 0 ? 0 : N - 1;
+            const double dt = tid == 0 ? 0.0 : dN, d = dt - shift;
+            const double A = keepA ? Arow[i] : 1.0;
+            if (keepA && A < f.a_collapse) col = 1;
             mn = fmin(mn, A);
             chk = fma(q_at(i), 0.0, chk);
             chk = fma(A, 0.0, chk);
-            chk = fma(dl, 0.0, chk);
-            for (int d = 0; d < 2; ++d) {
-                if (!dst[d]) continue;
-                dst[d][2 * f.total + c.off + i] = A;
-                dst[d][4 * f.total + c.off + i] = m;
-            }
-        }
-        __syncthreads();  // all reads of the delta~ scratch are done
-        for (int i = i0; i < i1; ++i) {
-            const double dl = (i == N - 1) ? ((f.gauge == 0) ? 0.0 : dN) : dscr[i] - shift;
-            for (int d = 0; d < 2; ++d)
-                if (dst[d]) dst[d][3 * f.total + c.off + i] = dl;
+            chk = fma(d, 0.0, chk);
+            put(2, i, A);
+            put(3, i, d);
+            put(4, i, tid == 0 ? 0.0 : 24.0 * h24 * tot2 / exp(-d));
         }
     } else {
-        for (int i = i0; i < i1; ++i) {
-            chk = fma(q_at(i), 0.0, chk);
-            for (int d = 0; d < 2; ++d) {
-                if (!dst[d]) continue;
-                double* o = dst[d];
-                o[2 * f.total + c.off + i] = 1.0;
-                o[3 * f.total + c.off + i] = 0.0;
-                o[4 * f.total + c.off + i] = 0.0;
-            }
+        for (int i = tid; i < N; i += blockDim.x) {
+            chk = fma(Phi[i] * Phi[i] + Pi[i] * Pi[i], 0.0, chk);
+            put(2, i, 1.0);
+            put(3, i, 0.0);
+            put(4, i, 0.0);
         }
     }
-    if (dst[1]) {
-        double* o = dst[1];
-        for (int i = i0; i < i1; ++i) {
-            o[c.off + i] = Phi[i];
-            o[f.total + c.off + i] = Pi[i];
+    if (dst[1])
+        for (int i = tid; i < N; i += blockDim.x) {
+            dst[1][i] = Phi[i];
+            dst[1][f.total + i] = Pi[i];
         }
-    }
     if (!isfinite(chk) || !isfinite(dN)) col |= 2;
     if (1.0 < f.a_collapse) col |= 1;
     // block reductions of min A and the flags
     for (int d = 32; d >= 1; d >>= 1) mn = fmin(mn, __shfl_xor(mn, d, 64));
     const int wcol = __any(col & 1) ? 1 : 0;
     const int wnf = __any(col & 2) ? 2 : 0;
-    __syncthreads();
     if ((tid & 63) == 0) {
-        sh[8 + (tid >> 6)] = mn;
+        sh[2][tid >> 6] = mn;  // (last read before the tiles' barriers; with the metric frozen never)
         ish[tid >> 6] = wcol | wnf;
     }
     __syncthreads();
     if (tid == 0) {
         double mA = 1.0;
         int fl = 0;
-        for (int w = 0; w < 4; ++w) {
-            mA = fmin(mA, sh[8 + w]);
+        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
+            mA = fmin(mA, sh[2][w]);
             fl |= ish[w];
         }
         if (f.final_) {
             InstStatus o = st;
             o.minA = mA;
-            o.mass = f.frozen ? 0.0 : h * tot2 / ((f.gauge == 0) ? 1.0 : exp(-dN));
+            o.mass = f.frozen ? 0.0 : c.h * tot2 / ((f.gauge == 0) ? 1.0 : exp(-dN));
             if (o.state == ST_RUNNING || o.state == ST_DONE) {
                 if (fl & 2) {
                     o.state = ST_NONFINITE;
@@ -289,86 +298,30 @@ __global__ void __launch_bounds__(256) finalize_kernel(FinArgs f)
     }
 }
 
-__device__ double block_reduce(double v, bool take_max, double* sh)
+// Maximum of non-negative values over the block (up to 16 wavefronts), on thread 0.
+// nan: a NaN among them is kept (else it is passed over).
+__device__ double block_max(double v, bool nan, double* sh)
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    for (int d = 32; d >= 1; d >>= 1) {
-        const double o = __shfl_xor(v, d, 64);
-        v = take_max ? fmax(v, o) : v + o;
-    }
+    auto worse = [&](double a, double o) -> double { return (nan && !(o == o)) ? o : (nan && !(a == a)) ? a : fmax(a, o); };
+    for (int d = 32; d >= 1; d >>= 1) v = worse(v, __shfl_xor(v, d, 64));
     __syncthreads();
     if (lane == 0) sh[wv] = v;
     __syncthreads();
-    double r = take_max ? 0.0 : 0.0;
-    for (int w = 0; w < nw; ++w) r = take_max ? fmax(r, sh[w]) : r + sh[w];
+    double r = sh[0];
+    for (int w = 1; w < nw; ++w) r = worse(r, sh[w]);
     return r;
 }
 
-// Residuals of Eqs. (5)-(6) at interior points and the mass integral of Sec. II,
-// into columns 0, 1, 3, 4 of out [n_inst][5].  One 256-thread block per instance.
-__global__ void __launch_bounds__(256) diagnostics_kernel(int n_inst, const InstConst* ic, const double* Phi,
-                                                          const double* Pi, const double* A,
-                                                          const double* delta, const double* m, double* out)
-{
-    __shared__ double sh[8];
-    const int b = blockIdx.x;
-    const InstConst c = ic[b];
-    const int N = c.N;
-    const double h = c.h;
-    const double* Ph = Phi + c.off;
-    const double* Pq = Pi + c.off;
-    const double* Aa = A + c.off;
-    const double* dd = delta + c.off;
-    // ghosts: A even about 0, A - 1 odd about pi/2; delta even about both ends
-    auto Ag = [&](int i) -> double {
-        if (i < 0) return Aa[-i];
-        if (i > N - 1) return 2.0 - Aa[2 * (N - 1) - i];
-        return Aa[i];
-    };
-    auto dg = [&](int i) -> double {
-        if (i < 0) return dd[-i];
-        if (i > N - 1) return dd[2 * (N - 1) - i];
-        return dd[i];
-    };
-    // integrand tan^2 x A q, even about both ends, zero at both ends
-    auto mg = [&](int i) -> double {
-        if (i < 0) i = -i;
-        if (i > N - 1) i = 2 * (N - 1) - i;
-        if (i == 0 || i == N - 1) return 0.0;
-        const double t = tan((double)i * h);
-        return t * t * Aa[i] * (Ph[i] * Ph[i] + Pq[i] * Pq[i]);
-    };
-    double rA = 0.0, rd = 0.0, M = 0.0;
-    for (int i = threadIdx.x; i < N - 1; i += blockDim.x) {
-        M += h * (-mg(i - 1) + 13.0 * mg(i) + 13.0 * mg(i + 1) - mg(i + 2)) / 24.0;
-        if (i >= 1) {
-            const double x = (double)i * h;
-            const double s = sin(x), co = cos(x);
-            const double sc = s * co;
-            const double q = Ph[i] * Ph[i] + Pq[i] * Pq[i];
-            const double DA = (Ag(i - 2) - 8.0 * Ag(i - 1) + 8.0 * Ag(i + 1) - Ag(i + 2)) / (12.0 * h);
-            const double Dd = (dg(i - 2) - 8.0 * dg(i - 1) + 8.0 * dg(i + 1) - dg(i + 2)) / (12.0 * h);
-            const double ra = DA - ((1.0 + 2.0 * s * s) / sc * (1.0 - Aa[i]) - sc * Aa[i] * q);
-            const double rdl = Dd + sc * q;
-            rA = fmax(rA, fabs(ra));
-            rd = fmax(rd, fabs(rdl));
-        }
-    }
-    rA = block_reduce(rA, true, sh);
-    rd = block_reduce(rd, true, sh);
-    M = block_reduce(M, false, sh);
-    if (threadIdx.x == 0) {
-        out[b * 5 + 0] = rA;
-        out[b * 5 + 1] = rd;
-        out[b * 5 + 3] = m[c.off + N - 1];
-        out[b * 5 + 4] = M;
-    }
-}
-
+// Diagnostics of the packed state (Phi, Pi, A, delta, m) of the current step, whose
+// metric is the constraint solve of (Phi, Pi), into out [n_inst][5]: the residuals
+// of Eqs. (5)-(6) at interior points (columns 0, 1), of Eq. (4) (2), the mass
+// m(pi/2) (3) and the mass integral of Sec. II (4).
+//
 // Residual of Eq. (4), A_t = -2 sin x cos x A^2 e^-delta Phi Pi, which the
-// evolution never imposes (Sec. II monitors the residuals of its equations).
+// evolution never imposes (Sec. II monitors the residuals of its equations):
 // A_t is the time derivative of the discrete A of the constraint solve along
-// the semi-discrete flow: the derivative of A(Phi, Pi) in the direction of the
+// the semi-discrete flow, the derivative of A(Phi, Pi) in the direction of the
 // right-hand sides (Phi_t, Pi_t) of Eqs. (2)-(3), taken through each step of
 // the solve (q = Phi^2 + Pi^2, p = sin x cos x q, delta~ = -prefix cell rule of
 // p, E = e^-delta, sigma = tan^2 x q E, S = prefix cell rule of sigma,
@@ -379,171 +332,152 @@ __global__ void __launch_bounds__(256) diagnostics_kernel(int n_inst, const Inst
 //   m_t = (S_t - m E_t) / E,  A_t = -cos^3 x / sin x m_t.
 // E is e^-delta of the gauge-shifted delta: m_t is homogeneous of degree 0 in
 // a constant factor of E, S and their derivatives, so the shift drops out.
-// Input: the packed state (Phi, Pi, A, delta, m) of the current step, whose
-// metric is the constraint solve of (Phi, Pi).  One 256-thread block per
-// instance, thread t owning a run of consecutive points; `scr` holds two
-// doubles per packed point: X = p_t for the whole kernel, Y = q_t of the own
-// points, then sigma_t (each thread overwrites only its own entries, and the
-// neighbours read Y only after the barrier that follows).  delta~_t is formed
-// twice from X with the same carry, so it needs no storage.
-// out[b*5 + 2] = max over interior points of |A_t + 2 sin x cos x A^2
-// e^-delta Phi Pi|; NaN with the metric frozen (A is then held, not solved).
-__global__ void __launch_bounds__(256) adot_residual_kernel(int n_inst, const InstConst* ic,
-                                                            const double* state5, int64_t total, int frozen,
-                                                            double ko, double* scr, double* out)
+// Column 2 is max over interior points of |A_t + 2 sin x cos x A^2 e^-delta Phi
+// Pi|; NaN with the metric frozen (A is then held, not solved).
+//
+// One block per instance; the interior points go in tiles of kDiagTile, kDiagK
+// consecutive ones per thread.  First loop: the fluxes of a tile and two points on
+// each side into LDS (one exponential per point), the right-hand sides, and q_t, p_t
+// into `scr` (two doubles per packed point).  Second loop: both prefix sums side by
+// side, their sums carried over the tiles; a thread forms sigma_t at its
+// neighbours' adjacent points itself.  The mass integral's 4-point rule sums to
+// h sum tan^2 x A q (the integrand is even and 0 at both ends).
+// Bound by the latency of the loads and scans of a tile: one instance of 1025
+// points 16 us, the 1024-instance batch (1025 to 4097) 124, against 61 and 1085 in
+// two kernels with 256 threads, a run of N/256 points each and about eight tangents
+// and thirteen exponentials per point.
+constexpr int kDiagK = 4, kDiagThreads = 512, kDiagTile = kDiagK * kDiagThreads;
+
+__global__ void __launch_bounds__(kDiagThreads) diagnostics_kernel(const InstConst* ic, const double* const* nats,
+                                                                   const double* state5, int64_t total, int frozen,
+                                                                   double ko, double* scr, double* out)
 {
-    __shared__ double sh[16];
-    const int b = blockIdx.x;
-    if (b >= n_inst) return;
+    __shared__ double sf[kDiagTile + 4], sgx[kDiagTile + 4];  // f1 and g of points t0 - 2 ..
+    __shared__ double sh[3][16];
+    constexpr int K = kDiagK;
+    const int b = blockIdx.x, tid = threadIdx.x;
     const InstConst c = ic[b];
     const int N = c.N;
-    const double h = c.h;
-    if (frozen) {
-        if (threadIdx.x == 0) out[b * 5 + 2] = __builtin_nan("");
-        return;
-    }
-    const double* Ph = state5 + c.off;
-    const double* Pq = state5 + total + c.off;
-    const double* Aa = state5 + 2 * total + c.off;
-    const double* dd = state5 + 3 * total + c.off;
-    const double* mm = state5 + 4 * total + c.off;
-    double* X = scr + c.off;
-    double* Y = scr + total + c.off;
-    const double kof = ko / (64.0 * h), i12h = 1.0 / (12.0 * h);
-    auto t2_at = [&](int i) -> double {
-        const double t = tan((double)i * h);
-        return t * t;
+    const double h24 = c.h24, i12h = c.i12h, kof = ko / (64.0 * c.h);
+    const ADSCL_GLOBAL double* const Ph = gmem(state5 + c.off);
+    const ADSCL_GLOBAL double* const Pq = gmem(state5 + total + c.off);
+    const ADSCL_GLOBAL double* const Aa = gmem(state5 + 2 * total + c.off);
+    const ADSCL_GLOBAL double* const dd = gmem(state5 + 3 * total + c.off);
+    const ADSCL_GLOBAL double* const mm = gmem(state5 + 4 * total + c.off);
+    const ADSCL_GLOBAL double* const nat = gmem(nats[b]);
+    ADSCL_GLOBAL double* const X = gmem(scr + c.off);          // p_t
+    ADSCL_GLOBAL double* const Y = gmem(scr + total + c.off);  // q_t
+    // the point a ghost mirrors; sl, sr: the sign it takes left of x = 0, right of pi/2
+    auto mir = [&](int i, double sl, double sr, double& sg) -> int {
+        sg = i < 0 ? sl : (i > N - 1 ? sr : 1.0);
+        return i < 0 ? -i : (i > N - 1 ? 2 * (N - 1) - i : i);
     };
     // Phi odd about 0, even about pi/2; Pi even about 0, odd about pi/2
-    auto phg = [&](int i) -> double {
-        if (i < 0) return -Ph[-i];
-        if (i > N - 1) return Ph[2 * (N - 1) - i];
-        return Ph[i];
-    };
-    auto pig = [&](int i) -> double {
-        if (i < 0) return Pq[-i];
-        if (i > N - 1) return -Pq[2 * (N - 1) - i];
-        return Pq[i];
-    };
+    auto phg = [&](int i) -> double { double sg; const int j = mir(i, -1.0, 1.0, sg); return sg * Ph[j]; };
+    auto pig = [&](int i) -> double { double sg; const int j = mir(i, 1.0, -1.0, sg); return sg * Pq[j]; };
+    // A even about 0, A - 1 odd about pi/2; delta even about both ends
+    auto Ag = [&](int i) -> double { double sg; const int j = mir(i, 1.0, -1.0, sg); return sg > 0.0 ? Aa[j] : 2.0 - Aa[j]; };
+    auto dg = [&](int i) -> double { double sg; return dd[mir(i, 1.0, 1.0, sg)]; };
     auto w_at = [&](int i) -> double { return Aa[i] * exp(-dd[i]); };
-    // f1 = w Pi: even about 0, odd about pi/2
-    auto f1g = [&](int i) -> double {
-        if (i < 0) return w_at(-i) * Pq[-i];
-        if (i > N - 1) {
-            const int j = 2 * (N - 1) - i;
-            return -(w_at(j) * Pq[j]);
-        }
-        return w_at(i) * Pq[i];
-    };
-    // g = tan^2 x w Phi up to N - 2, the even 6th-order extrapolation at N - 1;
-    // odd about 0, even about pi/2
-    auto g_in = [&](int i) -> double {
-        if (i == N - 1) {
-            const double g2 = t2_at(N - 2) * (w_at(N - 2) * Ph[N - 2]);
-            const double g3 = t2_at(N - 3) * (w_at(N - 3) * Ph[N - 3]);
-            const double g4 = t2_at(N - 4) * (w_at(N - 4) * Ph[N - 4]);
-            return (15.0 * g2 - 6.0 * g3 + g4) / 10.0;
-        }
-        return t2_at(i) * (w_at(i) * Ph[i]);
-    };
-    auto gg = [&](int i) -> double {
-        if (i < 0) return -g_in(-i);
-        if (i > N - 1) return g_in(2 * (N - 1) - i);
-        return g_in(i);
-    };
+    auto g_in = [&](int i) -> double { return nat[kNatT2 * N + i] * (w_at(i) * Ph[i]); };
     auto ko7 = [&](auto&& u, int i) -> double {
         return kof * (u(i - 3) - 6.0 * u(i - 2) + 15.0 * u(i - 1) - 20.0 * u(i) + 15.0 * u(i + 1) - 6.0 * u(i + 2)
                       + u(i + 3));
     };
     auto d5 = [&](auto&& u, int i) -> double { return (u(i - 2) - 8.0 * u(i - 1) + 8.0 * u(i + 1) - u(i + 2)) * i12h; };
 
-    const int tid = threadIdx.x;
-    const int C = (N + 255) / 256;
-    const int i0 = tid * C;
-    const int i1 = min(N, i0 + C);
-    // right-hand sides of Eqs. (2)-(3) (pinned points 0 except Pi at the origin),
-    // q_t and p_t at the own points
-    for (int i = i0; i < i1; ++i) {
-        double rPh = 0.0, rPi = 0.0;
-        if (i >= 1 && i <= N - 2) {
-            const double t = tan((double)i * h);
-            rPh = d5(f1g, i) + ko7(phg, i);
-            rPi = (1.0 / (t * t)) * d5(gg, i) + ko7(pig, i);
-        } else if (i == 0) {
-            // lim tan^-2 x (tan^2 x f2)' = 3 f2'(0), f2 = w Phi odd about 0
-            const double f21 = w_at(1) * Ph[1], f22 = w_at(2) * Ph[2];
-            rPi = 3.0 * ((16.0 * f21 - 2.0 * f22) * i12h) + ko7(pig, 0);
+    double rA = 0.0, rd = 0.0, rt = 0.0, T = 0.0;
+    for (int t0 = 1; t0 <= N - 2; t0 += kDiagTile) {
+        if (!frozen) {
+            __syncthreads();  // the last tile's readers are done
+            for (int k = tid; k < kDiagTile + 4; k += kDiagThreads) {
+                const int i = t0 - 2 + k;
+                if (i > N) break;
+                // f1 = w Pi: even about 0, odd about pi/2; g = tan^2 x w Phi up to N - 2,
+                // the even 6th-order extrapolation at N - 1: odd about 0, even about pi/2
+                double sg1, sg2;
+                const int j = mir(i, 1.0, -1.0, sg1);
+                mir(i, -1.0, 1.0, sg2);
+                const double w = w_at(j);
+                sf[k] = sg1 * (w * Pq[j]);
+                sgx[k] = j == N - 1 ? (15.0 * g_in(N - 2) - 6.0 * g_in(N - 3) + g_in(N - 4)) / 10.0
+                                    : sg2 * (nat[kNatT2 * N + j] * (w * Ph[j]));
+            }
+            __syncthreads();
         }
-        const double qt = 2.0 * (Ph[i] * rPh + Pq[i] * rPi);
-        const double x = (double)i * h;
-        X[i] = (i == 0 || i == N - 1) ? 0.0 : sin(x) * cos(x) * qt;
-        Y[i] = qt;
+        for (int k = tid; k < kDiagTile; k += kDiagThreads) {
+            const int i = t0 + k;
+            if (i > N - 2) break;
+            const double sc = nat[kNatSC * N + i], q = Ph[i] * Ph[i] + Pq[i] * Pq[i];
+            T += nat[kNatT2 * N + i] * Aa[i] * q;
+            rA = fmax(rA, fabs(d5(Ag, i) - (nat[kNatRA * N + i] * (1.0 - Aa[i]) - sc * Aa[i] * q)));
+            rd = fmax(rd, fabs(d5(dg, i) + sc * q));
+            if (!frozen) {
+                const double rPh = d5([&](int j) -> double { return sf[j - t0 + 2]; }, i) + ko7(phg, i);
+                const double rPi = nat[kNatCT2 * N + i] * d5([&](int j) -> double { return sgx[j - t0 + 2]; }, i) +
+                                   ko7(pig, i);
+                const double qt = 2.0 * (Ph[i] * rPh + Pq[i] * rPi);
+                X[i] = sc * qt;
+                Y[i] = qt;
+            }
+        }
     }
-    __syncthreads();
-    // delta~_t: 0 at x = 0, minus the prefix cell rule of p_t (odd about both
-    // ends), in the prefix form of the sum of cells (for an odd u with u_0 = 0
-    // the terms -u_{-1} - 12 u_0 + u_1 are 2 u_1)
-    auto ptg = [&](int i) -> double {
-        double sg = 1.0;
-        if (i < 0) { i = -i; sg = -1.0; }
-        if (i > N - 1) { i = 2 * (N - 1) - i; sg = -sg; }
-        return sg * X[i];
-    };
-    double ps = 0.0;
-    for (int i = i0; i < i1; ++i) ps += X[i];
     double tot;
-    const double carry = block_excl_scan(ps, sh, tot);
-    const double p1 = X[1];
-    auto dtil_t = [&](double Rk, int i) -> double {
-        return -(h / 24.0) * (24.0 * Rk - 12.0 * X[i] + ptg(i - 1) - ptg(i + 1) + 2.0 * p1);
-    };
-    double R = carry, ss = 0.0;
-    for (int i = i0; i < i1; ++i) {
-        R += X[i];
-        const double E = exp(-dd[i]);
-        const double Et = -E * dtil_t(R, i);
-        const double q = Ph[i] * Ph[i] + Pq[i] * Pq[i];
-        const double sg = (i == 0 || i == N - 1) ? 0.0 : t2_at(i) * (Y[i] * E + q * Et);
-        Y[i] = sg;
-        ss += sg;
-    }
+    block_scan(T, sh[2], tot);
     __syncthreads();
-    // S_t: 0 at x = 0, the prefix cell rule of sigma_t (even about both ends,
-    // 0 there); then m_t, A_t and the residual at interior points
-    auto sgg = [&](int i) -> double {
-        if (i < 0) i = -i;
-        if (i > N - 1) i = 2 * (N - 1) - i;
-        return Y[i];
-    };
-    double tot2;
-    const double carry2 = block_excl_scan(ss, sh + 4, tot2);
-    double R1 = carry, R2 = carry2, rmax = 0.0;
-    for (int i = i0; i < i1; ++i) {
-        R1 += X[i];
-        R2 += Y[i];
-        if (i == 0 || i == N - 1) continue;
-        const double St = (h / 24.0) * (24.0 * R2 - 12.0 * Y[i] + sgg(i - 1) - sgg(i + 1));
-        const double E = exp(-dd[i]);
-        const double Et = -E * dtil_t(R1, i);
-        const double mt = (St - mm[i] * Et) / E;
-        const double x = (double)i * h;
-        const double sn = sin(x), co = cos(x);
-        const double At = -(co * co * co / sn) * mt;
-        const double r = At + 2.0 * (sn * co) * Aa[i] * Aa[i] * E * Ph[i] * Pq[i];
-        rmax = fmax(rmax, fabs(r));
-        if (!(r == r)) rmax = r;  // keep a NaN
+    if (!frozen) {
+        // X past the ends is never needed: sigma_t is 0 there
+        auto in = [&](int i) -> bool { return i >= 1 && i <= N - 2; };
+        const double p1 = X[1];
+        double carry = 0.0, carry2 = 0.0;
+        for (int t0 = 1; t0 <= N - 2; t0 += kDiagTile) {
+            const int i0 = t0 + tid * K;
+            double x[K + 4], ps = 0.0;  // i0 - 2 .. i0 + K + 1
+#pragma unroll
+            for (int k = 0; k < K + 4; ++k) {
+                x[k] = in(i0 - 2 + k) ? X[i0 - 2 + k] : 0.0;
+                if (k >= 2 && k < K + 2) ps += x[k];
+            }
+            double tt;
+            double R = carry + block_scan(ps, sh[0], tt) - x[1];
+            carry += tt;
+            double E[K + 2], Et[K + 2], sg[K + 2], ss = 0.0;  // i0 - 1 .. i0 + K
+#pragma unroll
+            for (int k = 0; k < K + 2; ++k) {
+                const int i = i0 - 1 + k;
+                R += x[k + 1];
+                E[k] = Et[k] = sg[k] = 0.0;
+                if (in(i)) {
+                    E[k] = exp(-dd[i]);
+                    Et[k] = E[k] * (h24 * (24.0 * R - 12.0 * x[k + 1] + x[k] - x[k + 2] + 2.0 * p1));
+                    sg[k] = nat[kNatT2 * N + i] * (Y[i] * E[k] + (Ph[i] * Ph[i] + Pq[i] * Pq[i]) * Et[k]);
+                }
+                if (k >= 1 && k < K + 1) ss += sg[k];
+            }
+            double R2 = carry2 + block_scan(ss, sh[1], tt);
+            carry2 += tt;
+#pragma unroll
+            for (int k = 1; k < K + 1; ++k) {
+                const int i = i0 - 1 + k;
+                if (i > N - 2) break;
+                R2 += sg[k];
+                const double St = h24 * (24.0 * R2 - 12.0 * sg[k] + sg[k - 1] - sg[k + 1]);
+                const double mt = (St - mm[i] * Et[k]) / E[k];
+                const double r = -nat[kNatC3S * N + i] * mt +
+                                 2.0 * nat[kNatSC * N + i] * Aa[i] * Aa[i] * E[k] * Ph[i] * Pq[i];
+                rt = (r == r) ? fmax(rt, fabs(r)) : r;  // keep a NaN
+            }
+        }
     }
-    for (int d = 32; d >= 1; d >>= 1) {
-        const double o = __shfl_xor(rmax, d, 64);
-        rmax = (o == o) ? fmax(rmax, o) : o;
-    }
-    __syncthreads();
-    if ((tid & 63) == 0) sh[8 + (tid >> 6)] = rmax;
-    __syncthreads();
+    rA = block_max(rA, false, sh[2]);
+    rd = block_max(rd, false, sh[2]);
+    rt = frozen ? __builtin_nan("") : block_max(rt, true, sh[2]);
     if (tid == 0) {
-        double r = 0.0;
-        for (int w = 0; w < 4; ++w) r = (sh[8 + w] == sh[8 + w]) ? fmax(r, sh[8 + w]) : sh[8 + w];
-        out[b * 5 + 2] = r;
+        out[b * 5 + 0] = rA;
+        out[b * 5 + 1] = rd;
+        out[b * 5 + 2] = rt;
+        out[b * 5 + 3] = mm[N - 1];
+        out[b * 5 + 4] = c.h * tot;
     }
 }
 
@@ -583,13 +517,14 @@ hipError_t launch_set_targets(int n_inst, const InstConst* ic, InstStatus* st, i
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(int n_inst, const InstConst* ic, InstStatus* st, double* state5, int64_t total,
-                           int gauge, int frozen, double a_collapse, bool final, int32_t snap_every,
-                           int32_t n_slots, double* snaps, hipStream_t s, int32_t a_reint)
+hipError_t launch_finalize(int n_inst, int64_t max_N, const InstConst* ic, InstStatus* st, const double* const* nat,
+                           double* state5, int64_t total, int gauge, int frozen, double a_collapse, bool final,
+                           int32_t snap_every, int32_t n_slots, double* snaps, hipStream_t s, int32_t a_reint)
 {
     FinArgs f;
     f.ic = ic;
     f.st = st;
+    f.nat = nat;
     f.state5 = state5;
     f.total = total;
     f.a_collapse = a_collapse;
@@ -600,21 +535,16 @@ hipError_t launch_finalize(int n_inst, const InstConst* ic, InstStatus* st, doub
     f.frozen = frozen;
     f.final_ = final ? 1 : 0;
     f.a_reint = a_reint;
-    finalize_kernel<<<dim3(n_inst), dim3(256), 0, s>>>(f);
+    // one tile for the largest grid where 1024 threads hold it
+    const int waves = (int)std::min<int64_t>(16, (max_N - 2 + 64 * kFinK - 1) / (64 * kFinK));
+    finalize_kernel<<<dim3(n_inst), dim3(64 * waves), 0, s>>>(f);
     return hipGetLastError();
 }
 
-hipError_t launch_diagnostics(int n_inst, const InstConst* ic, const double* Phi, const double* Pi,
-                              const double* A, const double* delta, const double* m, double* out, hipStream_t s)
+hipError_t launch_diagnostics(int n_inst, const InstConst* ic, const double* const* nat, const double* state5,
+                              int64_t total, int frozen, double ko, double* scr, double* out, hipStream_t s)
 {
-    diagnostics_kernel<<<dim3(n_inst), dim3(256), 0, s>>>(n_inst, ic, Phi, Pi, A, delta, m, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_adot_residual(int n_inst, const InstConst* ic, const double* state5, int64_t total, int frozen,
-                                double ko, double* scr, double* out, hipStream_t s)
-{
-    adot_residual_kernel<<<dim3(n_inst), dim3(256), 0, s>>>(n_inst, ic, state5, total, frozen, ko, scr, out);
+    diagnostics_kernel<<<dim3(n_inst), dim3(kDiagThreads), 0, s>>>(ic, nat, state5, total, frozen, ko, scr, out);
     return hipGetLastError();
 }
 

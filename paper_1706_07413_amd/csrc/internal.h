@@ -72,6 +72,10 @@ struct ClassCfg {
     int W;
 };
 
+// Tables of one N in grid order, [kNatTables][N], 0 at both ends: sin x cos x,
+// tan^2 x, cos^3 x/sin x, cot^2 x, (1 + 2 sin^2 x)/(sin x cos x).
+enum { kNatSC = 0, kNatT2 = 1, kNatC3S = 2, kNatCT2 = 3, kNatRA = 4, kNatTables = 5 };
+
 // Tables for one (N, P, W): three arrays sc, t2, ct2, each [P][64 W] with entry
 // (k, lane) = value at grid point lane*P + k (zero outside 1..N-2).
 size_t table_len(ClassCfg c);
@@ -155,16 +159,13 @@ hipError_t launch_set_targets(int n_inst, const InstConst* ic, InstStatus* st, i
 // to snapshot slot steps / snap_every when snapshots are on and due; when
 // `final`, an instance at its target is tested for collapse / non-finite data
 // and marked DONE at n_final.
-hipError_t launch_finalize(int n_inst, const InstConst* ic, InstStatus* st, double* state5, int64_t total,
-                           int gauge, int frozen, double a_collapse, bool final, int32_t snap_every,
-                           int32_t n_slots, double* snaps, hipStream_t s, int32_t a_reint = 0);
-// Diagnostics: out[b*4 + {0..3}] = max|R_A'|, max|R_delta'|, m(pi/2), M (cell rule).
-hipError_t launch_diagnostics(int n_inst, const InstConst* ic, const double* Phi, const double* Pi,
-                              const double* A, const double* delta, const double* m, double* out,
-                              hipStream_t s);
-// Residual of Eq. (4) into column 2 of out [n_inst][5]; scr: 2 * total doubles.
-hipError_t launch_adot_residual(int n_inst, const InstConst* ic, const double* state5, int64_t total, int frozen,
-                                double ko, double* scr, double* out, hipStream_t s);
+hipError_t launch_finalize(int n_inst, int64_t max_N, const InstConst* ic, InstStatus* st, const double* const* nat,
+                           double* state5, int64_t total, int gauge, int frozen, double a_collapse, bool final,
+                           int32_t snap_every, int32_t n_slots, double* snaps, hipStream_t s, int32_t a_reint = 0);
+// Diagnostics of the state [5][total] into out [n_inst][5] (diagnostics_kernel);
+// scr: 2 * total doubles.
+hipError_t launch_diagnostics(int n_inst, const InstConst* ic, const double* const* nat, const double* state5,
+                              int64_t total, int frozen, double ko, double* scr, double* out, hipStream_t s);
 
 // Fixed device scratch of the allocation-free entry point: 2^21 doubles
 // (16 MiB) per GPU, held until the process ends.  static_scratch_init looks up
