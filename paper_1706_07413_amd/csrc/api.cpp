@@ -4,7 +4,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -103,11 +102,12 @@ struct adscl_ctx {
     hipEvent_t fork = nullptr;  // start of a multi-class launch, recorded on `stream`
     int n_big = 0;              // classes holding one large (multi-workgroup) instance
     std::vector<BigGroup> big_groups;  // their launches
-    // spectrum rows for states laid out as [slot][5][total], grouped by N:
-    // (N, first row, rows) per group, for spec_slots slots
+    // spectrum rows for states laid out as [slot][5][total], and their tiles of one
+    // grid size each, for spec_slots slots
     int spec_slots = -1;
-    std::vector<std::array<int, 3>> spec_groups;
+    int spec_tiles = 0;
     SpecRow* d_spec_rows = nullptr;
+    SpecTile* d_spec_tiles = nullptr;
     bool initialized = false;
     std::string err;
 };
@@ -474,32 +474,38 @@ int run_finalize(adscl_ctx* c, bool final, int32_t snap_every, int32_t n_slots, 
     return ADSCL_OK;
 }
 
-// Spectrum rows of `n_slots` states laid out as [slot][5][total] (Phi, Pi, A,
-// ... rows), grouped by grid size; rebuilt when n_slots changes.  Synchronises.
+// Spectrum rows and tiles of `n_slots` states laid out as [slot][5][total] (Phi,
+// Pi, A, ... rows); rebuilt when n_slots changes.  Synchronises.
 int spec_rows(adscl_ctx* c, int n_slots)
 {
     if (c->spec_slots == n_slots) return ADSCL_OK;
     std::vector<SpecRow> rows;
-    c->spec_groups.clear();
-    for (const auto& kv : c->tables) {
-        const int N = kv.first;
+    std::vector<SpecTile> tiles;
+    std::map<int, std::vector<int>> of;  // instances per grid size
+    for (int b = 0; b < c->n_inst; ++b) of[c->N[b]].push_back(b);
+    for (const auto& kv : of) {
+        const NTables& t = c->tables[kv.first];
         const int first = (int)rows.size();
         for (int sl = 0; sl < n_slots; ++sl) {
             const int64_t base = (int64_t)sl * 5 * c->total;
-            for (int b = 0; b < c->n_inst; ++b) {
-                if (c->N[b] != N) continue;
+            for (const int b : kv.second)
                 rows.push_back(SpecRow{base + c->off[b], base + c->total + c->off[b], base + 2 * c->total + c->off[b],
                                        (int64_t)sl * c->n_inst + b});
-            }
         }
-        c->spec_groups.push_back({N, first, (int)rows.size() - first});
+        for (int r = first; r < (int)rows.size(); r += 16)
+            tiles.push_back(SpecTile{t.d_wPi, t.d_wPhi, kv.first, r, std::min(16, (int)rows.size() - r), 0});
     }
-    void* d;
-    int rc = buffer(c, "spec_rows", sizeof(SpecRow) * rows.size(), &d);
-    if (rc) return rc;
+    void *d, *dt;
+    int rc;
+    c->spec_slots = -1;
+    if ((rc = buffer(c, "spec_rows", sizeof(SpecRow) * rows.size(), &d))) return rc;
+    if ((rc = buffer(c, "spec_tiles", sizeof(SpecTile) * tiles.size(), &dt))) return rc;
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     HIP_TRY(c, hipMemcpy(d, rows.data(), sizeof(SpecRow) * rows.size(), hipMemcpyHostToDevice));
+    HIP_TRY(c, hipMemcpy(dt, tiles.data(), sizeof(SpecTile) * tiles.size(), hipMemcpyHostToDevice));
     c->d_spec_rows = (SpecRow*)d;
+    c->d_spec_tiles = (SpecTile*)dt;
+    c->spec_tiles = (int)tiles.size();
     c->spec_slots = n_slots;
     return ADSCL_OK;
 }
@@ -507,11 +513,7 @@ int spec_rows(adscl_ctx* c, int n_slots)
 // Spectra of the states at `base` (the layout spec_rows was built for).
 int run_spectrum(adscl_ctx* c, const double* base, int J, double* E, double* Pihat, double* Phihat)
 {
-    for (const auto& g : c->spec_groups) {
-        const NTables& t = c->tables[g[0]];
-        HIP_TRY(c, launch_spectrum_rows(base, c->d_spec_rows + g[1], g[2], g[0], t.d_wPi, t.d_wPhi, J, E, Pihat,
-                                        Phihat, c->stream));
-    }
+    HIP_TRY(c, launch_spectrum(base, c->d_spec_rows, c->d_spec_tiles, c->spec_tiles, J, E, Pihat, Phihat, c->stream));
     return ADSCL_OK;
 }
 

@@ -182,11 +182,20 @@ struct SpecRow {
     int64_t a;
     int64_t out;
 };
-// Projection of sqrt(A) Pi, sqrt(A) Phi of `n_rows` rows of grid size N on the
-// weight tables wPi = h t2 e_j, wPhi = h t2 e_j'/omega_j ([Jtab][N]); outputs
-// [out][J] (any may be NULL).  FP64 MFMA.
-hipError_t launch_spectrum_rows(const double* base, const SpecRow* rows, int n_rows, int N, const double* wPi,
-                                const double* wPhi, int J, double* E, double* Pihat, double* Phihat, hipStream_t s);
+// Up to 16 rows of one grid size N, rows[first, first + rows), with the weight
+// tables wPi = h t2 e_j, wPhi = h t2 e_j'/omega_j ([Jtab][N]).
+struct SpecTile {
+    const double* wPi;
+    const double* wPhi;
+    int32_t N;
+    int32_t first;
+    int32_t rows;
+    int32_t pad;
+};
+// Projection of sqrt(A) Pi, sqrt(A) Phi of the tiles' rows on the weight tables;
+// outputs [out][J] (any may be NULL).  FP64 MFMA.
+hipError_t launch_spectrum(const double* base, const SpecRow* rows, const SpecTile* tiles, int n_tiles, int J, double* E,
+                           double* Pihat, double* Phihat, hipStream_t s);
 
 // ---- discrete adjoint -------------------------------------------------------
 

@@ -6,92 +6,109 @@
 //   E_rj = Pihat_rj^2 + Phihat_rj^2,
 // with wPi = h tan^2 x e_j(x), wPhi = h tan^2 x e_j'(x)/omega_j (zero at both
 // ends).  A row r is one state of one instance (an instance of the current
-// batch, or an instance in one snapshot slot); rows of one grid size N form one
+// batch, or an instance in one snapshot slot); rows of one grid size N form a
 // (rows x N) . (N x J) product, evaluated in 16 x 16 output tiles with
 // v_mfma_f64_16x16x4_f64: lane l supplies A[l % 16][l / 16] of the 16 x 4 block
 // and B[l / 16][l % 16] of the 4 x 16 block, and holds accumulators
 // D[l / 16 + 4 q][l % 16], q = 0..3.
 #include <math.h>
 
-#include "internal.h"
+#include "stage.h"
 
 namespace adscl {
 namespace {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-// One workgroup of four wavefronts per (16-row tile, 16-mode tile); the
-// wavefronts take interleaved 4-point slices of the contraction and their
-// partial tiles are summed through LDS in a fixed order.
-__global__ void __launch_bounds__(256) spectrum_mfma_kernel(const double* base, const SpecRow* rows, int n_rows,
-                                                            int N, const double* wPi, const double* wPhi, int J,
-                                                            double* E, double* Pihat, double* Phihat)
+constexpr int kWaves = 16;
+
+// One workgroup per (16-row tile, 16-mode tile), all tiles of all grid sizes in one
+// launch.  Its wavefronts take the contraction in turns of 16 points; lane l
+// supplies points 4 (l / 16) + t of a turn for the t-th of four products (the
+// order of the points is free as long as both operands agree), so that its loads of
+// a row are 32 consecutive bytes and four lanes' a whole line.  The partial
+// tiles are summed through LDS in a fixed order.
+// Bound by the latency of those loads, which is why sixteen wavefronts share a tile:
+// the contraction of one 16385-point state with 64 modes has only four tiles.
+// Measured: the 1024-instance batch (three grid sizes, 32 modes) 72 us against 364
+// with one launch per grid size and four wavefronts per tile that took turns of 4
+// points; 16 modes of one 4097-point state 40 against 143; 64 modes of five
+// 16385-point states 178 against 823.
+__global__ void __launch_bounds__(64 * kWaves) spectrum_mfma_kernel(const double* base, const SpecRow* rows,
+                                                                    const SpecTile* tiles, int J, double* E,
+                                                                    double* Pihat, double* Phihat)
 {
-    __shared__ double part[3][8][64];
+    __shared__ double part[kWaves][8][64];
+    const SpecTile T = tiles[blockIdx.x];
+    const int N = T.N;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int i = lane & 15, kk = lane >> 4;
-    const int r = blockIdx.x * 16 + i;  // row of the A operand this lane supplies
     const int j = blockIdx.y * 16 + i;  // mode of the B operand this lane supplies
-    const bool vr = r < n_rows, vj = j < J;
-    SpecRow R{0, 0, 0, 0};
-    if (vr) R = rows[r];
+    const bool vr = i < T.rows, vj = j < J;
+    const SpecRow R = rows[T.first + (vr ? i : 0)];  // row of the A operand this lane supplies
+    const ADSCL_GLOBAL double* const a = gmem(base + R.a + 4 * kk);
+    const ADSCL_GLOBAL double* const pi = gmem(base + R.pi + 4 * kk);
+    const ADSCL_GLOBAL double* const phi = gmem(base + R.phi + 4 * kk);
+    const ADSCL_GLOBAL double* const wp = gmem(T.wPi + (size_t)(vj ? j : 0) * N + 4 * kk);
+    const ADSCL_GLOBAL double* const wf = gmem(T.wPhi + (size_t)(vj ? j : 0) * N + 4 * kk);
     v4d cp = {0.0, 0.0, 0.0, 0.0}, cf = {0.0, 0.0, 0.0, 0.0};
-    for (int k0 = 4 * wv; k0 < N; k0 += 16) {
-        const int k = k0 + kk;
-        double ap = 0.0, af = 0.0, bp = 0.0, bf = 0.0;
-        if (k < N) {
-            if (vr) {
-                const double sA = sqrt(base[R.a + k]);
-                ap = sA * base[R.pi + k];
-                af = sA * base[R.phi + k];
-            }
-            if (vj) {
-                bp = wPi[(size_t)j * N + k];
-                bf = wPhi[(size_t)j * N + k];
-            }
-        }
-        cp = __builtin_amdgcn_mfma_f64_16x16x4f64(ap, bp, cp, 0, 0, 0);
-        cf = __builtin_amdgcn_mfma_f64_16x16x4f64(af, bf, cf, 0, 0, 0);
-    }
-    if (wv > 0) {
+    auto turn = [&](int k0, auto&& in) {
+        double va[4], vp[4], vf[4], bp[4], bf[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            part[wv - 1][q][lane] = cp[q];
-            part[wv - 1][4 + q][lane] = cf[q];
+        for (int t = 0; t < 4; ++t) {
+            const int k = in(t) ? k0 + t : 0;  // (a point past N - 1 loads another one's and is masked below)
+            va[t] = a[k];
+            vp[t] = pi[k];
+            vf[t] = phi[k];
+            bp[t] = wp[k];
+            bf[t] = wf[k];
         }
-    }
-    __syncthreads();
-    if (wv != 0) return;
 #pragma unroll
-    for (int w = 0; w < 3; ++w) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            cp[q] += part[w][q][lane];
-            cf[q] += part[w][4 + q][lane];
+        for (int t = 0; t < 4; ++t) {
+            const bool o = vr && in(t);
+            const double sA = sqrt(va[t]);
+            const double ap = o ? sA * vp[t] : 0.0, af = o ? sA * vf[t] : 0.0;
+            const double wp_ = vj && in(t) ? bp[t] : 0.0, wf_ = vj && in(t) ? bf[t] : 0.0;
+            cp = __builtin_amdgcn_mfma_f64_16x16x4f64(ap, wp_, cp, 0, 0, 0);
+            cf = __builtin_amdgcn_mfma_f64_16x16x4f64(af, wf_, cf, 0, 0, 0);
         }
-    }
-    // accumulator q of lane l is output row l / 16 + 4 q, column l % 16
-    const int col = blockIdx.y * 16 + (lane & 15);
+    };
+    int k0 = 16 * wv;
+#pragma unroll 2
+    for (; k0 + 16 <= N; k0 += 16 * kWaves) turn(k0, [](int) { return true; });
+    if (k0 < N) turn(k0, [&](int t) { return k0 + 4 * kk + t < N; });
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int row = blockIdx.x * 16 + (lane >> 4) + 4 * q;
-        if (row < n_rows && col < J) {
-            const size_t o = (size_t)rows[row].out * J + col;
-            if (Pihat) Pihat[o] = cp[q];
-            if (Phihat) Phihat[o] = cf[q];
-            if (E) E[o] = cp[q] * cp[q] + cf[q] * cf[q];
-        }
+        part[wv][q][lane] = cp[q];
+        part[wv][4 + q][lane] = cf[q];
+    }
+    __syncthreads();
+    // wavefront q finishes accumulator q: accumulator q of lane l is output row
+    // l / 16 + 4 q, column l % 16
+    if (wv >= 4) return;
+    double sp = 0.0, sf = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        sp += part[w][wv][lane];
+        sf += part[w][4 + wv][lane];
+    }
+    const int row = (lane >> 4) + 4 * wv, col = blockIdx.y * 16 + (lane & 15);
+    if (row < T.rows && col < J) {
+        const size_t o = (size_t)rows[T.first + row].out * J + col;
+        if (Pihat) Pihat[o] = sp;
+        if (Phihat) Phihat[o] = sf;
+        if (E) E[o] = sp * sp + sf * sf;
     }
 }
 
 }  // namespace
 
-hipError_t launch_spectrum_rows(const double* base, const SpecRow* rows, int n_rows, int N, const double* wPi,
-                                const double* wPhi, int J, double* E, double* Pihat, double* Phihat, hipStream_t s)
+hipError_t launch_spectrum(const double* base, const SpecRow* rows, const SpecTile* tiles, int n_tiles, int J, double* E,
+                           double* Pihat, double* Phihat, hipStream_t s)
 {
-    if (n_rows <= 0) return hipSuccess;
-    spectrum_mfma_kernel<<<dim3((n_rows + 15) / 16, (J + 15) / 16), dim3(256), 0, s>>>(base, rows, n_rows, N, wPi,
-                                                                                        wPhi, J, E, Pihat, Phihat);
+    if (n_tiles <= 0) return hipSuccess;
+    spectrum_mfma_kernel<<<dim3(n_tiles, (J + 15) / 16), dim3(64 * kWaves), 0, s>>>(base, rows, tiles, J, E, Pihat,
+                                                                                   Phihat);
     return hipGetLastError();
 }
 

@@ -1,6 +1,7 @@
-"""The kernels that finish a call (metric, status) and diagnose states, at the edges
-of their tiles: 4 points per thread, 64 threads per wavefront, up to 4096 (finalize)
-or 2048 (diagnostics) interior points per tile."""
+"""The kernels that finish a call (metric, status), diagnose and project states, at
+the edges of their tiles: 4 points per thread, 64 threads per wavefront, up to 4096
+(finalize) or 2048 (diagnostics) interior points per tile, 16 rows, modes and points
+per turn of the projection."""
 import numpy as np
 import pytest
 
@@ -55,3 +56,24 @@ def test_metric_and_diagnostics_at_tile_edges(gauge, alone):
             assert d[k, 3] == m[-1]
             assert abs(d[k, 4] - O.mass_paper(Phi, Pi, A)) <= 1e-12 * d[k, 4]
             o += N
+
+
+@pytest.mark.parametrize("N,rows,J", [(17, 1, 1), (257, 15, 16), (255, 16, 15), (259, 17, 17), (271, 33, 31),
+                                      (273, 2, 33), (1025, 3, 128), (4097, 1, 16)])
+def test_projection_at_tile_edges(N, rows, J):
+    rng = np.random.default_rng(7)
+    c = rng.uniform(-1.0, 1.0, size=(rows, min(J, 5)))
+    eps = rng.uniform(0.05, 0.1, size=rows)
+    print("projection", N, rows, J, flush=True)
+    b = adscl.Batch([N] * rows, n_modes=J, a_collapse=0.0)
+    b.init_modes(eps, c)
+    b.step(6, 1e9)
+    g = gpu_state(b)
+    E, P, F = b.spectrum(J)
+    b.close()
+    for r in range(rows):
+        s = slice(r * N, (r + 1) * N)
+        Eo, Po, Fo = O.spectrum(g["Phi"][s], g["Pi"][s], g["A"][s], J)
+        assert_close(P[r], Po, "Pihat row %d" % r)
+        assert_close(F[r], Fo, "Phihat row %d" % r)
+        assert_close(E[r], Eo, "E row %d" % r)
