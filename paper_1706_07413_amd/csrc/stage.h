@@ -216,20 +216,29 @@ struct Stage {
     static constexpr int SLOTS = P * RS;
     static_assert(P >= 4, "lane 0 must own grid points 0..3");
 
-    // Full lanes (EDGE: N - 1 = 64 W P) keep their own points in registers and take
+    // The edge path (EDGE: the forward kernels, and the adjoint on full lanes,
+    // N - 1 = 64 W P): lanes keep their own points in registers and take
     // their neighbours' edge values (the last / first three stage-input points,
     // p and sigma, the last / first two fluxes) across lanes with DPP wavefront
     // shifts; only lanes 0 and 63 go through small LDS slots (X*, and R* for the
     // adjoint's transposed stencils and reverse scans) to reach the adjacent
-    // wavefront.  Every other case exchanges whole lane-interleaved rows.  The
-    // forward edge kernel (FWD) keeps the coefficient tables in LDS (LT); the
+    // wavefront.  The adjoint on other grids exchanges whole lane-interleaved rows.
+    // The forward kernels (FWD) keep the coefficient tables in LDS (LT); the
     // adjoint reads them from global memory and keeps its own state in the LDS
-    // the rows would take.
-    static constexpr bool EDGE = FULL;
+    // the rows would take.  On grids that do not fill the lanes (RAG) points past
+    // N - 2 stay 0, and what their images past pi/2 would have added to the stencils of
+    // the last points is added to the right-hand sides afterwards (end_terms): the
+    // place of the end within a lane is not known at compile time, and choosing
+    // registers by it costs more instructions than the whole correction.
+    // Measured, one instance of 3001 / 2001 / 1001 / 201 points: 17.9, 12.3, 9.1 and
+    // 8.1 us per step, against 28.6, 19.2, 10.5 and 9.1 with whole rows in LDS, a fourth
+    // barrier per stage and the tables in L2 (full lanes: 15.6 at 4097, 8.2 at 1025).
+    static constexpr bool EDGE = FULL || FWD;
+    static constexpr bool RAG = EDGE && !FULL;
     static constexpr bool LT = FWD && EDGE;
     static constexpr bool ROWS = !EDGE;
     static constexpr size_t lds_doubles = (ROWS ? (size_t)4 * SLOTS + 2 * NL : 0)
-                                          + (EDGE ? (size_t)44 * (W + 2) + 20 * W : 0) + (LT ? (size_t)3 * P * NL : 0)
+                                          + (EDGE ? (size_t)44 * (W + 2) + 20 * W + (RAG ? 20 * P : 0) : 0) + (LT ? (size_t)3 * P * NL : 0)
                                           + 4 * W + 8 + 64;
 
     double2* U;     // (Phi_s, Pi_s) rows
@@ -251,6 +260,10 @@ struct Stage {
     double* RF;     // EDGE, adjoint: [W][4] cotangents of the D g rows, points 0, 1 of lane 0, P-1, P-2 of lane 63
     double* RSb;    // EDGE, adjoint: [W][2] S-bar of the first point of lane 0, of the last point of lane 63
     double* RDt;    // EDGE, adjoint: [W][2] the same for the delta~ cotangents
+    // RAG: the points of the two lanes from jb on that hold N - 4 .. N - 2
+    double2* GU;    // [2 buffers][2 P] their stage input
+    double2* GF;    // [2 buffers][2 P] their fluxes
+    double2* GR;    // [2 P] what end_terms adds to their right-hand sides
     double* T;      // LT: the coefficient tables, [3][P][64 W] as in global memory
     double* red;    // [0,W) delta~ totals, [W,2W) S totals, [2W,3W) flags,
                     // [3W,4W) spare, 4W: p_1, 4W+1: p_{N-2}
@@ -258,6 +271,8 @@ struct Stage {
     int tid, lane, wv, i0, col, N;
     int buf;        // XU buffer of the last publish (EDGE)
     bool has_nm2, near_end, bgauge;
+    int jb;         // RAG: see GU
+    bool at_end;    // RAG: this lane holds points past N - 2 that a stencil from the last points reaches
     double h, dt, h24, i12h, kof, thr;
     const ADSCL_GLOBAL double* tab0;
 
@@ -273,7 +288,7 @@ struct Stage {
                                           double a_collapse, int t)
     {
         double* p = lds;
-        U = F = XU = XF = RU = nullptr;
+        U = F = XU = XF = RU = GU = GF = GR = nullptr;
         PE = SE = XP = XS = T = RF = RSb = RDt = nullptr;
         if (ROWS) {
             U = reinterpret_cast<double2*>(p);
@@ -303,6 +318,12 @@ struct Stage {
             p += 2 * W;
             RDt = p;
             p += 2 * W;
+            if (RAG) {
+                GU = reinterpret_cast<double2*>(p);
+                GF = GU + 4 * P;
+                GR = GF + 4 * P;
+                p += 20 * P;
+            }
         }
         if (LT) {
             T = p;
@@ -330,6 +351,18 @@ struct Stage {
         // last lane owns N-4..N-2; otherwise lanes past N-2 idle and the end moves.
         has_nm2 = FULL ? (tid == NL - 1) : ((i0 <= N - 2) && (N - 2 < i0 + P));
         near_end = FULL ? (tid == NL - 1) : ((i0 + P + 2 >= N - 4) && (i0 <= N - 2));
+        at_end = false;
+        jb = 0;
+        if constexpr (RAG) {
+            jb = ((N - 2) / P - 1) * P;
+            near_end = i0 >= jb && i0 <= N - 2;  // the two lanes
+            at_end = i0 + P > N - 1 && i0 <= N + 1;
+            // past the last lane: zeros, as in every lane past the end
+            if (tid == 0) XP[2 * (W + 1)] = XS[2 * (W + 1)] = 0.0;
+            if (tid < 12) XU[(tid / 6 * (W + 2) + W + 1) * 6 + tid % 6] = make_double2(0.0, 0.0);
+            if (tid < 8) XF[(tid / 4 * (W + 2) + W + 1) * 4 + tid % 4] = make_double2(0.0, 0.0);
+            if (tid < 2 * P) GR[tid] = make_double2(0.0, 0.0);
+        }
         tab0 = gmem(tab);
         if constexpr (LT) {
             // each lane copies exactly the entries it reads later, so no barrier
@@ -345,6 +378,49 @@ struct Stage {
     static __device__ __forceinline__ double from_right(double v) { return dpp_d<0x130, 0xf>(v); }
 
     __device__ __forceinline__ bool own(int k) const { return FULL || (i0 + k <= N - 2); }
+
+    // The place of pi/2 relative to the lane's first point, opaque to the compiler:
+    // conditions on single points are then formed where they are used, by the
+    // wavefronts that meet them, instead of being kept as lane masks for the
+    // whole kernel (which spills scalar registers).
+    __device__ __forceinline__ int end_here() const
+    {
+        int e = N - 1 - i0;
+        asm volatile("" : "+v"(e));
+        return e;
+    }
+
+    // RAG: the points past N - 2 back to 0, and the terms of the images past pi/2
+    // (Phi even, Pi odd, f1 odd, g even about it; Phi = Pi = f1 = 0 there, g the even
+    // 6th-order extrapolation) in the stencils of N - 2 and N - 3.
+    __device__ __forceinline__ void end_terms(double* r0, double* r1) const
+    {
+        if (at_end) {
+            const int e = end_here();
+#pragma unroll
+            for (int k = 0; k < P; ++k)
+                if (k >= e) r0[k] = r1[k] = 0.0;
+        }
+        if (near_end) {
+            const int e = N - 2 - jb;
+            const double2 *gu = GU + buf * 2 * P + e, *gf = GF + buf * 2 * P + e;
+            const double2 v2 = gu[0], v3 = gu[-1], f2 = gf[0], f3 = gf[-1], f4 = gf[-2];
+            const int l2 = (N - 2) / P, l3 = (N - 3) / P;
+            const double c2 = T[(2 * P + (N - 2) - l2 * P) * NL + l2], c3 = T[(2 * P + (N - 3) - l3 * P) * NL + l3];
+            const double gext = (15.0 * f2.y - 6.0 * f3.y + f4.y) / 10.0;
+            // both lanes write the same; each then reads its own points
+            GR[e] = make_double2(fma(kof, fma(-6.0, v2.x, v3.x), i12h * f2.x),
+                                 fma(kof, fma(6.0, v2.y, -v3.y), c2 * (i12h * fma(8.0, gext, -f2.y))));
+            GR[e - 1] = make_double2(kof * v2.x, fma(-kof, v2.y, c3 * (-i12h * gext)));
+            const double2* const gr = GR + (i0 - jb);
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                const double2 g = gr[k];
+                r0[k] += g.x;
+                r1[k] += g.y;
+            }
+        }
+    }
 
     // LDS index of point j, -P <= j < 64 W P + P
     __device__ __forceinline__ int slot(int j) const
@@ -397,11 +473,17 @@ struct Stage {
 #pragma unroll
                 for (int r = 0; r < 3; ++r) g[3 + r] = make_double2(-v0[1 + r], v1[1 + r]);
             }
-            if (tid == NL - 1) {  // Phi = Pi = 0 at pi/2; Phi even, Pi odd about it: points N-1, N, N+1
+            if (FULL && tid == NL - 1) {  // Phi = Pi = 0 at pi/2; Phi even, Pi odd about it; points N-1, N, N+1
                 double2* g = XU + (buf * (W + 2) + W + 1) * 6;
                 g[0] = make_double2(0.0, 0.0);
                 g[1] = make_double2(v0[P - 1], -v1[P - 1]);
                 g[2] = make_double2(v0[P - 2], -v1[P - 2]);
+            }
+            if constexpr (RAG) {
+                if (near_end) {
+#pragma unroll
+                    for (int k = 0; k < P; ++k) GU[buf * 2 * P + i0 - jb + k] = make_double2(v0[k], v1[k]);
+                }
             }
             return;
         }
@@ -456,7 +538,7 @@ struct Stage {
             if (lane == 0) XP[2 * (wv + 1)] = p[0];
             if (lane == 63) XP[2 * (wv + 1) + 1] = p[P - 1];
             if (tid == 0) XP[1] = -p[1];                // p_{-1} = -p_1
-            if (tid == NL - 1) XP[2 * (W + 1)] = 0.0;  // p_{N-1} = 0
+            if (FULL && tid == NL - 1) XP[2 * (W + 1)] = 0.0;  // p_{N-1} = 0
         } else {
             PE[tid] = p[0];
             PE[NL + tid] = p[P - 1];
@@ -465,9 +547,10 @@ struct Stage {
         if (FULL) {
             if (tid == NL - 1) red[4 * W + 1] = p[P - 1];
         } else if (has_nm2) {
+            const int e = end_here() - 1;
 #pragma unroll
             for (int k = 0; k < P; ++k)
-                if (i0 + k == N - 2) red[4 * W + 1] = p[k];
+                if (k == e) red[4 * W + 1] = p[k];
         }
         __syncthreads();  // B1
         double carry, tot;
@@ -508,7 +591,7 @@ struct Stage {
             if (lane == 0) XS[2 * (wv + 1)] = sg[0];
             if (lane == 63) XS[2 * (wv + 1) + 1] = sg[P - 1];
             if (tid == 0) XS[1] = sg[1];                // sigma_{-1} = sigma_1
-            if (tid == NL - 1) XS[2 * (W + 1)] = 0.0;  // sigma_{N-1} = 0
+            if (FULL && tid == NL - 1) XS[2 * (W + 1)] = 0.0;  // sigma_{N-1} = 0
         } else {
             SE[tid] = sg[0];
             SE[NL + tid] = sg[P - 1];
@@ -556,7 +639,7 @@ struct Stage {
             if (lane == 0) XP[2 * (wv + 1)] = p[0];
             if (lane == 63) XP[2 * (wv + 1) + 1] = p[P - 1];
             if (tid == 0) XP[1] = -p[1];                // p_{-1} = -p_1
-            if (tid == NL - 1) XP[2 * (W + 1)] = 0.0;  // p_{N-1} = 0
+            if (FULL && tid == NL - 1) XP[2 * (W + 1)] = 0.0;  // p_{N-1} = 0
         } else {
             PE[tid] = p[0];
             PE[NL + tid] = p[P - 1];
@@ -565,9 +648,10 @@ struct Stage {
         if (FULL) {
             if (tid == NL - 1) red[4 * W + 1] = p[P - 1];
         } else if (has_nm2) {
+            const int e = end_here() - 1;
 #pragma unroll
             for (int k = 0; k < P; ++k)
-                if (i0 + k == N - 2) red[4 * W + 1] = p[k];
+                if (k == e) red[4 * W + 1] = p[k];
         }
         __syncthreads();  // B1
         double carry, tot;
@@ -621,6 +705,7 @@ struct Stage {
                                        double* av = nullptr, double* wout = nullptr, bool reint = false)
     {
         if constexpr (EDGE) return rhs_edge<KEEP, EVA>(check, frozen, v0, v1, r0, r1, ES, ks, av, wout, reint);
+        static_assert(EDGE || !EVA, "an evolved A: forward kernels only");
         __syncthreads();  // B0
         const auto tb = tables();
         double ko0[P], ko1[P], q[P];
@@ -845,10 +930,16 @@ struct Stage {
                 XFb[2] = make_double2(ff[1], -fg[1]);
                 XFb[3] = make_double2(ff[2], -fg[2]);
             }
-            if (tid == NL - 1) {
+            if (FULL && tid == NL - 1) {
                 // f1_{N-1} = 0, g_{N-1} the even 6th-order extrapolation; ghost N
                 XFb[(W + 1) * 4] = make_double2(0.0, (15.0 * fg[P - 1] - 6.0 * fg[P - 2] + fg[P - 3]) / 10.0);
                 XFb[(W + 1) * 4 + 1] = make_double2(-ff[P - 1], fg[P - 1]);
+            }
+            if constexpr (RAG) {
+                if (near_end) {
+#pragma unroll
+                    for (int k = 0; k < P; ++k) GF[buf * 2 * P + i0 - jb + k] = make_double2(ff[k], fg[k]);
+                }
             }
         }
         if (check) {
@@ -921,6 +1012,7 @@ struct Stage {
             r0[0] = 0.0;
             r1[0] = 3.0 * ((16.0 * f2_1 - 2.0 * f2_2) * i12h) + ko1[0];
         }
+        if constexpr (RAG) end_terms(r0, r1);
         return 0;
     }
 };

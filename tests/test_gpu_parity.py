@@ -389,3 +389,33 @@ def test_qp_family_temperatures_match_the_paper():
         r = O.evolve(Phi, Pi, 0)
         Eo, _, _ = O.spectrum(Phi, Pi, r["A"], J)
         assert abs(Tg - temperature(Eo)) <= 1e-12 * temperature(Eo)
+
+
+# The end of a grid that does not fill its lanes, in every place it can take: each
+# even point of a lane of 8 and of 4, the first and last lane of a wavefront
+# (2561, 2563, 2555; 513 + 258 = 771 ...), the smallest grid and all but full ones.
+RAGGED_ENDS = [17, 19, 21, 255, 259, 261, 263, 511, 515, 769, 771, 773, 1023, 1537, 1539, 2047, 2051, 2053, 2055, 2057,
+               2555, 2561, 2563, 4095]
+
+
+@pytest.mark.parametrize("rk,K,frozen", [(4, 0, False), (4, 0, True), (3, 0, False), (2, 3, False), (4, 5, False)])
+def test_ends_of_ragged_grids(rk, K, frozen):
+    print("ragged ends", rk, K, frozen, flush=True)
+    rng = np.random.default_rng(23)
+    eps = rng.uniform(0.5, 2.0, len(RAGGED_ENDS))
+    c = rng.uniform(-1.0, 1.0, (len(RAGGED_ENDS), 3))  # modes: data that reach the boundary
+    n = 40
+    b = adscl.Batch(RAGGED_ENDS, n_modes=3, rk_order=rk, a_reint=K, a_collapse=0.0,
+                    flags=adscl.FROZEN_METRIC if frozen else 0)
+    b.init_modes(0.1 * eps, c)
+    b.step(n, 1e9)
+    g, st = gpu_state(b), b.status()
+    b.close()
+    o = 0
+    for i, N in enumerate(RAGGED_ENDS):
+        Phi, Pi = O.init_modes(N, 0.1 * eps[i], c[i])
+        ref = O.evolve_scheme(Phi, Pi, n, rk=rk, a_reint=K, frozen=frozen)
+        assert st["steps"][i] == n
+        for f in ("Phi", "Pi") if frozen else FIELDS:
+            assert_close(g[f][o:o + N], ref[f], "N=%d rk %d K %d %s" % (N, rk, K, f))
+        o += N
