@@ -134,7 +134,10 @@ constexpr int kFinK = 4;  // consecutive points per thread
 // boundary gauge's shift enters every exponential), the second the two prefix sums
 // side by side.  A thread forms p and sigma at its neighbours' adjacent points
 // itself (two more exponentials for its four) instead of exchanging them, so that
-// two scans are a tile's only barriers; the coefficients come from tables in grid order.
+// two scans are a tile's only barriers; the coefficients come from tables in grid
+// order.  The order of every sum is that of threads of four points, whatever the
+// block's size (which follows the batch's largest grid), so that an instance's
+// results do not hang on the batch it is in.
 // Bound by the latency of those scans and of the loads: one instance of 513, 1025,
 // 16385 and 32769 points 9.1, 9.9, 54 and 92 us, against 18, 28, 342 and 608 with
 // 256 threads, a run of N/256 points each, and sin, cos, tan and three exponentials
@@ -173,7 +176,12 @@ __global__ void __launch_bounds__(1024) finalize_kernel(FinArgs f)
         double tot = 0.0;
         {
             double s = 0.0;
-            for (int i = 1 + tid; i <= N - 2; i += blockDim.x) s += nat[kNatSC * N + i] * q_at(i);
+            for (int t0 = 1; t0 <= N - 2; t0 += tile)
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const int i = t0 + tid * K + k;
+                    if (i <= N - 2) s += nat[kNatSC * N + i] * q_at(i);
+                }
             block_scan(s, sh[2], tot);
         }
         const double p1 = nat[kNatSC * N + 1] * q_at(1), pN2 = nat[kNatSC * N + N - 2] * q_at(N - 2);

@@ -77,3 +77,22 @@ def test_projection_at_tile_edges(N, rows, J):
         assert_close(P[r], Po, "Pihat row %d" % r)
         assert_close(F[r], Fo, "Phihat row %d" % r)
         assert_close(E[r], Eo, "E row %d" % r)
+
+
+@pytest.mark.parametrize("gauge", [O.GAUGE_BOUNDARY, O.GAUGE_ORIGIN])
+def test_a_grid_is_finished_alike_alone_and_beside_larger_ones(gauge):
+    """The block is sized for the batch's largest grid: the sums of a smaller one
+    must not depend on it, bit for bit."""
+    N, big = 129, [129, 2049, 4097]
+    Phi, Pi = O.init_gaussian(N, 3.0, 0.2)
+    got = []
+    for grids in ([N], big[:2], big):
+        b = adscl.Batch(grids, gauge=gauge, a_collapse=0.0)
+        rest = np.zeros(sum(grids[1:]))
+        b.init(np.concatenate([Phi, rest]), np.concatenate([Pi, rest]))
+        g, m = gpu_state(b), b.status()["minA"][0]
+        b.close()
+        got.append([g[f][:N] for f in FIELDS] + [m])
+    for other in got[1:]:
+        for f, x, y in zip(FIELDS + ("minA",), got[0], other):
+            assert np.array_equal(x, y), f
