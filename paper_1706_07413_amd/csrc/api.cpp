@@ -643,7 +643,8 @@ int adj_plan(adscl_ctx* c, double T, int64_t K, int J, AdjPlan& pl)
     if ((rc = buffer(c, "ckpt", sizeof(double) * ck_off[n], &ck))) return rc;
     if (pl.stored) {
         if ((rc = buffer(c, "keep", sizeof(double) * keep_off[n], &keep))) return rc;
-        seg_off.assign(n + 1, 0);  // no per-step states needed
+        seg_off.assign(n + 1, 0);  // no per-step states needed, nor scratch to recompute stages in
+        stg_off.assign(n + 1, 0);
     }
     if ((rc = buffer(c, "seg", sizeof(double) * seg_off[n], &seg))) return rc;
     if ((rc = buffer(c, "stage", sizeof(double) * stg_off[n], &stg))) return rc;

@@ -4,12 +4,9 @@
 // One workgroup owns one instance for the whole call and keeps its state on
 // chip: lane l owns the P consecutive grid points l*P .. l*P+P-1 and holds U^n,
 // the RK4 accumulator and the Kreiss-Oliger terms of its points in registers.
-// On grids that fill every lane (N - 1 = 64 W P) the stage input stays in
+// The stage input stays in
 // registers too and neighbours' values cross lanes by DPP, with small LDS
-// slots between wavefronts (no B0 below); otherwise the stage input and the
-// fluxes are exchanged through lane-interleaved LDS rows.  A stage is
-//   B0  stage input (Phi_s, Pi_s) with parity ghosts in LDS; every lane reads
-//       its +-3 window: Kreiss-Oliger terms and q = Phi^2 + Pi^2.
+// slots between wavefronts.  A stage is
 //   B1  delta~ = -int sin x cos x q  (Eq. (6)) as one prefix sum of
 //       p = sin x cos x q: lane-serial sums, a DPP wavefront scan, and the
 //       wavefront totals through LDS; then the end correction of the 4-point
@@ -17,9 +14,9 @@
 //   B2  S = int tan^2 x q e^{-delta} as a second prefix sum (Eq. (5) through
 //       m = (1 - A) sin x / cos^3 x), and A e^{-delta} = e^{-delta} - cos^3 x/sin x S.
 //   B3  fluxes f1 = A e^-delta Pi and g = tan^2 x A e^-delta Phi with parity
-//       ghosts in LDS; each lane applies the centred D stencil to its points
-//       (Eqs. (2)-(3)), does the RK4 combination and publishes the next stage
-//       input.
+//       ghosts in LDS; each lane applies the centred D and the Kreiss-Oliger
+//       stencils to its points (Eqs. (2)-(3)), does the RK4 combination and
+//       publishes the next stage input.
 // Between the first and the last step of a segment nothing goes to HBM but
 // the coefficient-table reads (L2-resident); the segment ends at the call's
 // last step or at the next snapshot step, where the finalize kernel solves the
@@ -128,7 +125,6 @@ struct Run {
                 cv1[k] = un1[k];
             }
         }
-        // every lane read U_s before B3, so U_{s+1} may replace it now
         sg.publish(cv0, cv1);
         return false;
     }
@@ -241,8 +237,8 @@ __global__ void __launch_bounds__(64 * W) evolve_pair_kernel(EvolveArgs a, int n
     // whole wavefronts and no wavefront passes a barrier of the branch it skips
     const bool loaded = __builtin_amdgcn_readfirstlane((b >= 0) && r.init(a, b, lds + half * HL, t)) != 0;
     bool run = loaded;
-    // a stage of Stage::rhs on the edge path passes this many barriers
-    const int nbar = Stage<P, WH, true, true>::edge_barriers(a.frozen != 0);
+    // a stage of Stage::rhs passes this many barriers
+    const int nbar = Stage<P, WH, true, true>::rhs_barriers(a.frozen != 0);
     auto idle = [&]() {
 #pragma unroll 1
         for (int i = 0; i < nbar; ++i) __syncthreads();

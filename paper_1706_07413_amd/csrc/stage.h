@@ -3,12 +3,9 @@
 // Sec. II), shared by the forward evolution kernel and the reverse (adjoint)
 // kernel, which recomputes forward stages.
 //
-// Lane l of the workgroup owns the P consecutive grid points l*P .. l*P+P-1.
-// LDS rows are lane-interleaved: point j = l*P + k sits in row k, column l + 1,
-// so the P reads of a lane's own points and the reads of its neighbours' edge
-// points are consecutive across lanes (no bank conflicts).  Column 0 holds the
-// ghosts left of x = 0, column NL + 1 the points past the last lane (the end
-// point and its ghosts when N - 1 = 64 W P, "FULL").
+// Lane l of the workgroup owns the P consecutive grid points l*P .. l*P+P-1 and
+// keeps them in registers; neighbours' edge points cross lanes by DPP, and
+// wavefronts through small LDS slots.
 //
 // Prefix-sum form of the cell rule: with C_i = h(-u_{i-1}+13u_i+13u_{i+1}-u_{i+2})/24
 // and R_k = sum_{j<=k} u_j,
@@ -179,53 +176,53 @@ __device__ __forceinline__ LaneArr<P, NL> lane_arr(ADSCL_GLOBAL double* base, in
 }
 
 // One step's stage record for the adjoint: for RK stage s (0..3) and point k of
-// lane l, the stage input (Phi, Pi), e^-delta and S side by side, 32 bytes at
-// ((s P + k) 64 W + l) 32, so that a 128-byte line holds four lanes' whole
-// entries (one load brings a stage's other fields of those lanes along).  The
-// same scalar base and opaque lane offset as LaneArr.
+// lane l, the stage input (Phi, Pi) in plane 0 and (e^-delta, w = A e^-delta) in plane 1,
+// [s][plane][P][64 W] pairs of doubles, so that a wavefront's access to either
+// pair of a point is 1 KB of whole lines and each plane can be loaded when its
+// registers fall free.  The same opaque lane offset as LaneArr, on a base that
+// is uniform for each (plane, k).
+typedef double pair_t __attribute__((ext_vector_type(2)));
 template <int P, int NL>
 struct StageRec {
     ADSCL_GLOBAL char* base;
     unsigned o;
-    __device__ __forceinline__ ADSCL_GLOBAL double* at(int s, int k) const
+    __device__ __forceinline__ ADSCL_GLOBAL pair_t* at(int plane, int k) const
     {
-        return (ADSCL_GLOBAL double*)(base + (o + (unsigned)((s * P + k) * NL * 32)));
+        ADSCL_GLOBAL char* p = base + (unsigned)((plane * P + k) * NL * 16);
+        asm("" : "+s"(p));  // a scalar address, not one more vector add
+        return (ADSCL_GLOBAL pair_t*)(p + o);
     }
-    __device__ __forceinline__ double ld(int s, int f, int k) const { return at(s, k)[f]; }
-    typedef double pair_t __attribute__((ext_vector_type(2)));
-    __device__ __forceinline__ void st(int s, int k, double v0, double v1, double e, double sv) const
+    __device__ __forceinline__ pair_t ld(int plane, int k) const { return *at(plane, k); }
+    __device__ __forceinline__ void st(int k, double v0, double v1, double e, double w) const
     {
-        ADSCL_GLOBAL pair_t* p = reinterpret_cast<ADSCL_GLOBAL pair_t*>(at(s, k));
-        p[0] = pair_t{v0, v1};
-        p[1] = pair_t{e, sv};
+        *at(0, k) = pair_t{v0, v1};
+        *at(1, k) = pair_t{e, w};
     }
 };
 
+// The stage's part of a record, at the uniform address `stage`, as seen by a lane.
 template <int P, int NL>
-__device__ __forceinline__ StageRec<P, NL> stage_rec(ADSCL_GLOBAL double* base, int lane_id)
+__device__ __forceinline__ StageRec<P, NL> stage_rec(ADSCL_GLOBAL double* stage, int lane_id)
 {
-    unsigned o = (unsigned)lane_id * 32u;
+    unsigned o = (unsigned)lane_id * 16u;
     asm volatile("" : "+v"(o));
-    return StageRec<P, NL>{(ADSCL_GLOBAL char*)base, o};
+    return StageRec<P, NL>{(ADSCL_GLOBAL char*)stage, o};
 }
 
 template <int P, int W, bool FULL, bool FWD = false>
 struct Stage {
     static constexpr int NL = 64 * W;
-    static constexpr int RS = NL + 2;
-    static constexpr int SLOTS = P * RS;
     static_assert(P >= 4, "lane 0 must own grid points 0..3");
 
-    // The edge path (EDGE: the forward kernels, and the adjoint on full lanes,
-    // N - 1 = 64 W P): lanes keep their own points in registers and take
+    // Lanes keep their own points in registers and take
     // their neighbours' edge values (the last / first three stage-input points,
     // p and sigma, the last / first two fluxes) across lanes with DPP wavefront
     // shifts; only lanes 0 and 63 go through small LDS slots (X*, and R* for the
     // adjoint's transposed stencils and reverse scans) to reach the adjacent
-    // wavefront.  The adjoint on other grids exchanges whole lane-interleaved rows.
-    // The forward kernels (FWD) keep the coefficient tables in LDS (LT); the
-    // adjoint reads them from global memory and keeps its own state in the LDS
-    // the rows would take.  On grids that do not fill the lanes (RAG) points past
+    // wavefront.
+    // The forward kernels (FWD) keep the coefficient tables in LDS; the
+    // adjoint reads them from global memory and keeps its own state in LDS.
+    // On grids that do not fill the lanes (RAG) points past
     // N - 2 stay 0, and what their images past pi/2 would have added to the stencils of
     // the last points is added to the right-hand sides afterwards (end_terms): the
     // place of the end within a lane is not known at compile time, and choosing
@@ -233,19 +230,11 @@ struct Stage {
     // Measured, one instance of 3001 / 2001 / 1001 / 201 points: 17.9, 12.3, 9.1 and
     // 8.1 us per step, against 28.6, 19.2, 10.5 and 9.1 with whole rows in LDS, a fourth
     // barrier per stage and the tables in L2 (full lanes: 15.6 at 4097, 8.2 at 1025).
-    static constexpr bool EDGE = FULL || FWD;
-    static constexpr bool RAG = EDGE && !FULL;
-    static constexpr bool LT = FWD && EDGE;
-    static constexpr bool ROWS = !EDGE;
-    static constexpr size_t lds_doubles = (ROWS ? (size_t)4 * SLOTS + 2 * NL : 0)
-                                          + (EDGE ? (size_t)44 * (W + 2) + 20 * W + (RAG ? 20 * P : 0) : 0) + (LT ? (size_t)3 * P * NL : 0)
-                                          + 4 * W + 8 + 64;
+    static constexpr bool RAG = !FULL;
+    static constexpr size_t lds_doubles = (size_t)44 * (W + 2) + (FWD ? 0 : 20 * (W + 2)) + (RAG ? 20 * P : 0)
+                                          + (FWD ? (size_t)3 * P * NL : 0) + 4 * W + 8 + 64;
 
-    double2* U;     // (Phi_s, Pi_s) rows
-    double2* F;     // (f1, g) rows; p first / last per lane between B0 and B2
-    double* PE;
-    double* SE;     // sigma first / last per lane
-    // EDGE slots, one per wavefront (slot wv + 1) plus two ghost slots: slot 0
+    // Edge slots, one per wavefront (slot wv + 1) plus two ghost slots: slot 0
     // holds the parity images left of x = 0 as if a wavefront -1 had written
     // them, slot W + 1 the end point and its images past pi/2, so that every
     // wavefront reads its two neighbours' slots the same way
@@ -256,20 +245,21 @@ struct Stage {
                     // the buffer follows XU's, since with the metric frozen B3 is the only
                     // barrier of a stage and a wavefront may write its next stage's fluxes
                     // while its neighbour still reads this stage's
-    double2* RU;    // EDGE, adjoint: [W][6] row cotangents (Phi_t, Pi_t) of points 0..2 of lane 0, P-1..P-3 of lane 63
-    double* RF;     // EDGE, adjoint: [W][4] cotangents of the D g rows, points 0, 1 of lane 0, P-1, P-2 of lane 63
-    double* RSb;    // EDGE, adjoint: [W][2] S-bar of the first point of lane 0, of the last point of lane 63
-    double* RDt;    // EDGE, adjoint: [W][2] the same for the delta~ cotangents
+    // the adjoint's slots, laid out the same way, their ghosts 0 throughout:
+    double2* RU;    // [W+2][6] row cotangents (Phi_t, Pi_t) of points 0..2 of lane 0, P-1..P-3 of lane 63
+    double* RF;     // [W+2][4] cotangents of the D g rows, points 0, 1 of lane 0, P-1, P-2 of lane 63
+    double* RSb;    // [W+2][2] S-bar of the first point of lane 0, of the last point of lane 63
+    double* RDt;    // [W+2][2] the same for the delta~ cotangents
     // RAG: the points of the two lanes from jb on that hold N - 4 .. N - 2
     double2* GU;    // [2 buffers][2 P] their stage input
     double2* GF;    // [2 buffers][2 P] their fluxes
     double2* GR;    // [2 P] what end_terms adds to their right-hand sides
-    double* T;      // LT: the coefficient tables, [3][P][64 W] as in global memory
-    double* red;    // [0,W) delta~ totals, [W,2W) S totals, [2W,3W) flags,
-                    // [3W,4W) spare, 4W: p_1, 4W+1: p_{N-2}
+    double* T;      // FWD: the coefficient tables, [3][P][64 W] as in global memory
+    double* red;    // [0,W) delta~ totals, [W,2W) S totals, [2W,3W) flags (the adjoint: cotangent totals),
+                    // [3W,4W) the adjoint's origin cotangent, 4W: p_1, 4W+1: p_{N-2}
     double* X64;    // 2^(j/64), j = 0..63, the table of exp_tab
-    int tid, lane, wv, i0, col, N;
-    int buf;        // XU buffer of the last publish (EDGE)
+    int tid, lane, wv, i0, N;
+    int buf;        // XU buffer of the last publish
     bool has_nm2, near_end, bgauge;
     int jb;         // RAG: see GU
     bool at_end;    // RAG: this lane holds points past N - 2 that a stencil from the last points reaches
@@ -288,44 +278,33 @@ struct Stage {
                                           double a_collapse, int t)
     {
         double* p = lds;
-        U = F = XU = XF = RU = GU = GF = GR = nullptr;
-        PE = SE = XP = XS = T = RF = RSb = RDt = nullptr;
-        if (ROWS) {
-            U = reinterpret_cast<double2*>(p);
-            F = U + SLOTS;
-            // F is free from B0 (its last readers finished the previous stage)
-            // until the flux writes after B2 (the edge path keeps its p edges in
-            // XP; the adjoint's reverse writes PE only after a barrier that
-            // follows its last reads of F)
-            PE = reinterpret_cast<double*>(F);
-            SE = reinterpret_cast<double*>(F + SLOTS);
-            p = SE + 2 * NL;
-        }
-        if (EDGE) {
-            XU = reinterpret_cast<double2*>(p);
-            p += 24 * (W + 2);
-            XP = p;
-            p += 2 * (W + 2);
-            XS = p;
-            p += 2 * (W + 2);
-            XF = reinterpret_cast<double2*>(p);
-            p += 16 * (W + 2);
+        XU = reinterpret_cast<double2*>(p);
+        p += 24 * (W + 2);
+        XP = p;
+        p += 2 * (W + 2);
+        XS = p;
+        p += 2 * (W + 2);
+        XF = reinterpret_cast<double2*>(p);
+        p += 16 * (W + 2);
+        RU = GU = GF = GR = nullptr;
+        RF = RSb = RDt = T = nullptr;
+        if constexpr (!FWD) {
             RU = reinterpret_cast<double2*>(p);
-            p += 12 * W;
+            p += 12 * (W + 2);
             RF = p;
-            p += 4 * W;
+            p += 4 * (W + 2);
             RSb = p;
-            p += 2 * W;
+            p += 2 * (W + 2);
             RDt = p;
-            p += 2 * W;
-            if (RAG) {
-                GU = reinterpret_cast<double2*>(p);
-                GF = GU + 4 * P;
-                GR = GF + 4 * P;
-                p += 20 * P;
-            }
+            p += 2 * (W + 2);
         }
-        if (LT) {
+        if (RAG) {
+            GU = reinterpret_cast<double2*>(p);
+            GF = GU + 4 * P;
+            GR = GF + 4 * P;
+            p += 20 * P;
+        }
+        if (FWD) {
             T = p;
             p += 3 * P * NL;
         }
@@ -346,7 +325,6 @@ struct Stage {
         thr = a_collapse;
         bgauge = gauge == 0;
         i0 = tid * P;
-        col = tid + 1;
         // FULL: N - 1 == 64 W P, so every lane owns P evolved points and the
         // last lane owns N-4..N-2; otherwise lanes past N-2 idle and the end moves.
         has_nm2 = FULL ? (tid == NL - 1) : ((i0 <= N - 2) && (N - 2 < i0 + P));
@@ -363,8 +341,13 @@ struct Stage {
             if (tid < 8) XF[(tid / 4 * (W + 2) + W + 1) * 4 + tid % 4] = make_double2(0.0, 0.0);
             if (tid < 2 * P) GR[tid] = make_double2(0.0, 0.0);
         }
+        if constexpr (!FWD) {  // the ghost slots, read after a later barrier
+            if (tid < 12) RU[tid / 6 * (W + 1) * 6 + tid % 6] = make_double2(0.0, 0.0);
+            if (tid < 8) RF[tid / 4 * (W + 1) * 4 + tid % 4] = 0.0;
+            if (tid < 4) RSb[tid / 2 * (W + 1) * 2 + tid % 2] = RDt[tid / 2 * (W + 1) * 2 + tid % 2] = 0.0;
+        }
         tab0 = gmem(tab);
-        if constexpr (LT) {
+        if constexpr (FWD) {
             // each lane copies exactly the entries it reads later, so no barrier
 #pragma unroll
             for (int t = 0; t < 3 * P; ++t) T[t * NL + tid] = tab0[t * NL + tid];
@@ -406,8 +389,9 @@ struct Stage {
             const double2 *gu = GU + buf * 2 * P + e, *gf = GF + buf * 2 * P + e;
             const double2 v2 = gu[0], v3 = gu[-1], f2 = gf[0], f3 = gf[-1], f4 = gf[-2];
             const int l2 = (N - 2) / P, l3 = (N - 3) / P;
-            const double c2 = T[(2 * P + (N - 2) - l2 * P) * NL + l2], c3 = T[(2 * P + (N - 3) - l3 * P) * NL + l3];
-            const double gext = (15.0 * f2.y - 6.0 * f3.y + f4.y) / 10.0;
+            const int e2 = (2 * P + (N - 2) - l2 * P) * NL + l2, e3 = (2 * P + (N - 3) - l3 * P) * NL + l3;
+            const double c2 = FWD ? T[e2] : tab0[e2], c3 = FWD ? T[e3] : tab0[e3];
+            const double gext = (fma(15.0, f2.y, -6.0 * f3.y) + f4.y) / 10.0;
             // both lanes write the same; each then reads its own points
             GR[e] = make_double2(fma(kof, fma(-6.0, v2.x, v3.x), i12h * f2.x),
                                  fma(kof, fma(6.0, v2.y, -v3.y), c2 * (i12h * fma(8.0, gext, -f2.y))));
@@ -420,13 +404,6 @@ struct Stage {
                 r1[k] += g.y;
             }
         }
-    }
-
-    // LDS index of point j, -P <= j < 64 W P + P
-    __device__ __forceinline__ int slot(int j) const
-    {
-        const int l = (j >= 0) ? (j / P) : -1 - ((-1 - j) / P);
-        return (j - l * P) * RS + l + 1;
     }
 
     // Per-stage view of the coefficient tables: a uniform base and the lane's
@@ -447,7 +424,7 @@ struct Stage {
     // Table t (0 sin x cos x, 1 tan^2 x, 2 cot^2 x) at the lane's point k.
     __device__ __forceinline__ double tab(const TabView& v, int t, int k) const
     {
-        if constexpr (LT) return T[(t * P + k) * NL + tid];
+        if constexpr (FWD) return T[(t * P + k) * NL + tid];
         return *(const ADSCL_GLOBAL double*)(v.base + (v.o + (unsigned)((t * P + k) * NL * 8)));
     }
 
@@ -455,60 +432,34 @@ struct Stage {
     // Phi odd / Pi even about x = 0, Phi even / Pi odd about pi/2, Phi = Pi = 0 at pi/2.
     __device__ __forceinline__ void publish(const double* v0, const double* v1)
     {
-        if constexpr (EDGE) {
-            // neighbours within the wavefront read the registers; lanes 0 and 63
-            // leave their edge points for the adjacent wavefronts
-            buf ^= 1;
-            double2* xu = XU + (buf * (W + 2) + wv + 1) * 6;
-            if (lane == 0) {
+        // neighbours within the wavefront read the registers; lanes 0 and 63
+        // leave their edge points for the adjacent wavefronts
+        buf ^= 1;
+        double2* xu = XU + (buf * (W + 2) + wv + 1) * 6;
+        if (lane == 0) {
 #pragma unroll
-                for (int r = 0; r < 3; ++r) xu[r] = make_double2(v0[r], v1[r]);
-            }
-            if (lane == 63) {
-#pragma unroll
-                for (int r = 0; r < 3; ++r) xu[3 + r] = make_double2(v0[P - 1 - r], v1[P - 1 - r]);
-            }
-            if (tid == 0) {  // Phi odd, Pi even about x = 0: points -1, -2, -3
-                double2* g = XU + buf * (W + 2) * 6;
-#pragma unroll
-                for (int r = 0; r < 3; ++r) g[3 + r] = make_double2(-v0[1 + r], v1[1 + r]);
-            }
-            if (FULL && tid == NL - 1) {  // Phi = Pi = 0 at pi/2; Phi even, Pi odd about it; points N-1, N, N+1
-                double2* g = XU + (buf * (W + 2) + W + 1) * 6;
-                g[0] = make_double2(0.0, 0.0);
-                g[1] = make_double2(v0[P - 1], -v1[P - 1]);
-                g[2] = make_double2(v0[P - 2], -v1[P - 2]);
-            }
-            if constexpr (RAG) {
-                if (near_end) {
-#pragma unroll
-                    for (int k = 0; k < P; ++k) GU[buf * 2 * P + i0 - jb + k] = make_double2(v0[k], v1[k]);
-                }
-            }
-            return;
+            for (int r = 0; r < 3; ++r) xu[r] = make_double2(v0[r], v1[r]);
         }
+        if (lane == 63) {
 #pragma unroll
-        for (int k = 0; k < P; ++k)
-            if (own(k)) U[k * RS + col] = make_double2(v0[k], v1[k]);
-        if (tid == 0) {
-            U[(P - 1) * RS] = make_double2(-v0[1], v1[1]);
-            U[(P - 2) * RS] = make_double2(-v0[2], v1[2]);
-            U[(P - 3) * RS] = make_double2(-v0[3], v1[3]);
+            for (int r = 0; r < 3; ++r) xu[3 + r] = make_double2(v0[P - 1 - r], v1[P - 1 - r]);
         }
-        if (FULL) {
-            if (tid == NL - 1) {
-                U[0 * RS + NL + 1] = make_double2(0.0, 0.0);
-                U[1 * RS + NL + 1] = make_double2(v0[P - 1], -v1[P - 1]);
-                U[2 * RS + NL + 1] = make_double2(v0[P - 2], -v1[P - 2]);
-                U[3 * RS + NL + 1] = make_double2(v0[P - 3], -v1[P - 3]);
-            }
-        } else if (near_end) {
+        if (tid == 0) {  // Phi odd, Pi even about x = 0: points -1, -2, -3
+            double2* g = XU + buf * (W + 2) * 6;
 #pragma unroll
-            for (int k = 0; k < P; ++k) {
-                const int j = i0 + k;
-                if (j >= N - 4 && j <= N - 2) U[slot(2 * (N - 1) - j)] = make_double2(v0[k], -v1[k]);
+            for (int r = 0; r < 3; ++r) g[3 + r] = make_double2(-v0[1 + r], v1[1 + r]);
+        }
+        if (FULL && tid == NL - 1) {  // Phi = Pi = 0 at pi/2; Phi even, Pi odd about it; points N-1, N, N+1
+            double2* g = XU + (buf * (W + 2) + W + 1) * 6;
+            g[0] = make_double2(0.0, 0.0);
+            g[1] = make_double2(v0[P - 1], -v1[P - 1]);
+            g[2] = make_double2(v0[P - 2], -v1[P - 2]);
+        }
+        if constexpr (RAG) {
+            if (near_end) {
+#pragma unroll
+                for (int k = 0; k < P; ++k) GU[buf * 2 * P + i0 - jb + k] = make_double2(v0[k], v1[k]);
             }
-            if (has_nm2) U[slot(N - 1)] = make_double2(0.0, 0.0);
         }
     }
 
@@ -534,15 +485,10 @@ struct Stage {
         }
         const double incl = wave_incl_scan(ptot);
         if (lane == 63) red[wv] = incl;
-        if constexpr (EDGE) {
-            if (lane == 0) XP[2 * (wv + 1)] = p[0];
-            if (lane == 63) XP[2 * (wv + 1) + 1] = p[P - 1];
-            if (tid == 0) XP[1] = -p[1];                // p_{-1} = -p_1
-            if (FULL && tid == NL - 1) XP[2 * (W + 1)] = 0.0;  // p_{N-1} = 0
-        } else {
-            PE[tid] = p[0];
-            PE[NL + tid] = p[P - 1];
-        }
+        if (lane == 0) XP[2 * (wv + 1)] = p[0];
+        if (lane == 63) XP[2 * (wv + 1) + 1] = p[P - 1];
+        if (tid == 0) XP[1] = -p[1];                // p_{-1} = -p_1
+        if (FULL && tid == NL - 1) XP[2 * (W + 1)] = 0.0;  // p_{N-1} = 0
         if (tid == 0) red[4 * W] = p[1];
         if (FULL) {
             if (tid == NL - 1) red[4 * W + 1] = p[P - 1];
@@ -558,15 +504,10 @@ struct Stage {
         carry += incl - ptot;
         const double p1 = red[4 * W], pN2 = red[4 * W + 1];
         double pl, pr;
-        if constexpr (EDGE) {
-            // lanes 0 / 63 take the neighbouring wavefront's (or the ghost) slot
-            pl = dpp_old<0x138>(XP[2 * wv + 1], p[P - 1]);
-            pr = dpp_old<0x130>(XP[2 * (wv + 2)], p[0]);
-        } else {
-            pl = (tid > 0) ? PE[NL + tid - 1] : -p1;  // p_{-1} = -p_1
-            pr = (tid < NL - 1) ? PE[tid + 1] : 0.0;  // p_{N-1} = 0
-        }
-        dN = -h24 * (24.0 * tot + 2.0 * pN2 + 2.0 * p1);        // delta~_{N-1}
+        // lanes 0 / 63 take the neighbouring wavefront's (or the ghost) slot
+        pl = dpp_old<0x138>(XP[2 * wv + 1], p[P - 1]);
+        pr = dpp_old<0x130>(XP[2 * (wv + 2)], p[0]);
+        dN = -h24 * fma(24.0, tot, 2.0 * pN2 + 2.0 * p1);        // delta~_{N-1}
         const double shift = bgauge ? dN : 0.0;
         // -delta = h24 (24 R - 12 p + p_m - p_p + 2 p_1) + shift, with h24
         // distributed over the terms: one add and three FMAs per point
@@ -587,27 +528,17 @@ struct Stage {
         }
         const double incl2 = wave_incl_scan(stot);
         if (lane == 63) red[W + wv] = incl2;
-        if constexpr (EDGE) {
-            if (lane == 0) XS[2 * (wv + 1)] = sg[0];
-            if (lane == 63) XS[2 * (wv + 1) + 1] = sg[P - 1];
-            if (tid == 0) XS[1] = sg[1];                // sigma_{-1} = sigma_1
-            if (FULL && tid == NL - 1) XS[2 * (W + 1)] = 0.0;  // sigma_{N-1} = 0
-        } else {
-            SE[tid] = sg[0];
-            SE[NL + tid] = sg[P - 1];
-        }
+        if (lane == 0) XS[2 * (wv + 1)] = sg[0];
+        if (lane == 63) XS[2 * (wv + 1) + 1] = sg[P - 1];
+        if (tid == 0) XS[1] = sg[1];                // sigma_{-1} = sigma_1
+        if (FULL && tid == NL - 1) XS[2 * (W + 1)] = 0.0;  // sigma_{N-1} = 0
         __syncthreads();  // B2
         double carry2;
         wave_totals(red + W, carry2, tot2);
         carry2 += incl2 - stot;
         double sl, sr;
-        if constexpr (EDGE) {
-            sl = dpp_old<0x138>(XS[2 * wv + 1], sg[P - 1]);
-            sr = dpp_old<0x130>(XS[2 * (wv + 2)], sg[0]);
-        } else {
-            sl = (tid > 0) ? SE[NL + tid - 1] : sg[1];  // sigma_{-1} = sigma_1
-            sr = (tid < NL - 1) ? SE[tid + 1] : 0.0;    // sigma_{N-1} = 0
-        }
+        sl = dpp_old<0x138>(XS[2 * wv + 1], sg[P - 1]);
+        sr = dpp_old<0x130>(XS[2 * (wv + 2)], sg[0]);
         double R2 = carry2;
 #pragma unroll
         for (int k = 0; k < P; ++k) {
@@ -635,15 +566,10 @@ struct Stage {
         }
         const double incl = wave_incl_scan(ptot);
         if (lane == 63) red[wv] = incl;
-        if constexpr (EDGE) {
-            if (lane == 0) XP[2 * (wv + 1)] = p[0];
-            if (lane == 63) XP[2 * (wv + 1) + 1] = p[P - 1];
-            if (tid == 0) XP[1] = -p[1];                // p_{-1} = -p_1
-            if (FULL && tid == NL - 1) XP[2 * (W + 1)] = 0.0;  // p_{N-1} = 0
-        } else {
-            PE[tid] = p[0];
-            PE[NL + tid] = p[P - 1];
-        }
+        if (lane == 0) XP[2 * (wv + 1)] = p[0];
+        if (lane == 63) XP[2 * (wv + 1) + 1] = p[P - 1];
+        if (tid == 0) XP[1] = -p[1];                // p_{-1} = -p_1
+        if (FULL && tid == NL - 1) XP[2 * (W + 1)] = 0.0;  // p_{N-1} = 0
         if (tid == 0) red[4 * W] = p[1];
         if (FULL) {
             if (tid == NL - 1) red[4 * W + 1] = p[P - 1];
@@ -659,14 +585,9 @@ struct Stage {
         carry += incl - ptot;
         const double p1 = red[4 * W], pN2 = red[4 * W + 1];
         double pl, pr;
-        if constexpr (EDGE) {
-            pl = dpp_old<0x138>(XP[2 * wv + 1], p[P - 1]);
-            pr = dpp_old<0x130>(XP[2 * (wv + 2)], p[0]);
-        } else {
-            pl = (tid > 0) ? PE[NL + tid - 1] : -p1;
-            pr = (tid < NL - 1) ? PE[tid + 1] : 0.0;
-        }
-        dN = -h24 * (24.0 * tot + 2.0 * pN2 + 2.0 * p1);
+        pl = dpp_old<0x138>(XP[2 * wv + 1], p[P - 1]);
+        pr = dpp_old<0x130>(XP[2 * (wv + 2)], p[0]);
+        dN = -h24 * fma(24.0, tot, 2.0 * pN2 + 2.0 * p1);
         const double shift = bgauge ? dN : 0.0;
         const double a24 = 24.0 * h24, a12 = -12.0 * h24, c0 = fma(2.0 * h24, p1, shift);
         double R = carry;
@@ -681,201 +602,44 @@ struct Stage {
         }
     }
 
-    // Right-hand sides of Eqs. (2)-(3) at the published stage input: barrier B0,
-    // Kreiss-Oliger terms and q from the +-3 window, the constraint solve (B1,
-    // B2), the fluxes f1 = A e^-delta Pi, g = tan^2 x A e^-delta Phi with parity
-    // ghosts (B3), the centred D stencil.  With `check`, the division-free test
+    // Barriers one call of rhs passes (EVA off): B1, B2 and B3, or B3 alone with the
+    // metric frozen.
+    static __device__ __forceinline__ int rhs_barriers(bool frozen) { return frozen ? 1 : 3; }
+
+    // Right-hand sides of Eqs. (2)-(3) at the published stage input (v0, v1): q, the
+    // constraint solve (B1, B2), the fluxes f1 = A e^-delta Pi, g = tan^2 x A
+    // e^-delta Phi with parity ghosts (B3), the Kreiss-Oliger terms and the centred
+    // D stencil.  With `check`, the division-free test
     // e^-delta - cos^3 x/sin x S < thr e^-delta (A < thr) and a finiteness test
     // run before B3 and the function returns their workgroup-wide bits
     // (1 collapsed, 2 non-finite) without computing r when any is set.
     // r0, r1: Phi_t, Pi_t of the own points (0 at pinned points).  KEEP: also
-    // stores the stage input (v0, v1), e^-delta and S of the lane's points as
+    // stores the stage input (v0, v1), e^-delta and w = A e^-delta of the lane's points as
     // stage ks of the stage record ES (StageRec).
-    // v0, v1: the published stage input of the own points (read on the edge
-    // path, where it is not in LDS).
     // EVA (A evolved by Eq. (4), the paper's alternative to solving Eq. (5) at
     // every stage): the stage's A of the own points is `av`; only the first
     // prefix sum runs (delta from Eq. (6)), the fluxes take w = av e^-delta, the
     // collapse test is av < thr; with `reint` the full solve runs instead and
     // its A, 1 - cos^3 x/sin x S/e^-delta, replaces `av` (re-integration from
     // Eq. (5)).  `wout` receives w = A e^-delta of the own points.
-    template <bool KEEP = false, bool EVA = false>
-    __device__ __forceinline__ int rhs(bool check, bool frozen, const double* v0, const double* v1, double* r0,
-                                       double* r1, ADSCL_GLOBAL double* ES = nullptr, int ks = 0,
-                                       double* av = nullptr, double* wout = nullptr, bool reint = false)
-    {
-        if constexpr (EDGE) return rhs_edge<KEEP, EVA>(check, frozen, v0, v1, r0, r1, ES, ks, av, wout, reint);
-        static_assert(EDGE || !EVA, "an evolved A: forward kernels only");
-        __syncthreads();  // B0
-        const auto tb = tables();
-        double ko0[P], ko1[P], q[P];
-        {
-            double2 w[P + 6];                        // points i0-3 .. i0+P+2
-#pragma unroll
-            for (int t = 0; t < P + 6; ++t) {
-                const int tt = t - 3;
-                if (tt < 0) w[t] = U[(P + tt) * RS + col - 1];
-                else if (tt < P) w[t] = U[tt * RS + col];
-                else w[t] = U[(tt - P) * RS + col + 1];
-            }
-#pragma unroll
-            for (int k = 0; k < P; ++k) {
-                ko0[k] = kof * (w[k].x - 6.0 * w[k + 1].x + 15.0 * w[k + 2].x - 20.0 * w[k + 3].x
-                                + 15.0 * w[k + 4].x - 6.0 * w[k + 5].x + w[k + 6].x);
-                ko1[k] = kof * (w[k].y - 6.0 * w[k + 1].y + 15.0 * w[k + 2].y - 20.0 * w[k + 3].y
-                                + 15.0 * w[k + 4].y - 6.0 * w[k + 5].y + w[k + 6].y);
-                // points past N-2 (general N only) may hold stale slots: keep them out
-                q[k] = own(k) ? w[k + 3].x * w[k + 3].x + w[k + 3].y * w[k + 3].y : 0.0;
-            }
-        }
-        double dl[P], E[P], S[P];
-        double dN = 0.0, tot2 = 0.0;
-        if (!frozen) {
-            if (EVA && !reint) {
-                delta_scan(q, dl, E, dN);
-#pragma unroll
-                for (int k = 0; k < P; ++k) S[k] = 0.0;
-            } else {
-                constraints(q, dl, E, S, dN, tot2);
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < P; ++k) { dl[k] = 0.0; E[k] = 1.0; S[k] = 0.0; }
-        }
-
-        // fluxes; c3s and tan^2 x are 0 at x = 0 in the tables, so w_0 = E_0, g_0 = 0
-        double f2_1 = 0.0, f2_2 = 0.0, chk = 0.0;
-        double fl[3] = {0.0, 0.0, 0.0}, gl[3] = {0.0, 0.0, 0.0};  // f1, g at N-2, N-3, N-4 (FULL)
-        double f1a[3] = {0.0, 0.0, 0.0}, ga[3] = {0.0, 0.0, 0.0}; // f1, g at points 1, 2 (lane 0)
-        int cl = 0;
-#pragma unroll
-        for (int k = 0; k < P; ++k) {
-            const int j = i0 + k;
-            if (own(k)) {
-                const double2 v = U[k * RS + col];
-                const double c3s = tab(tb, 2, k) * tab(tb, 0, k);
-                double wk;
-                if constexpr (EVA) {
-                    if (reint) av[k] = 1.0 - c3s * (S[k] / E[k]);
-                    wk = av[k] * E[k];
-                    wout[k] = wk;
-                } else {
-                    wk = E[k] - c3s * S[k];
-                }
-                const double f1 = wk * v.y;
-                const double f2 = wk * v.x;
-                const double g = tab(tb, 1, k) * f2;
-                if (k == 1) { f2_1 = f2; f1a[1] = f1; ga[1] = g; }
-                if (k == 2) { f2_2 = f2; f1a[2] = f1; ga[2] = g; }
-                if (k >= P - 3) { fl[P - 1 - k] = f1; gl[P - 1 - k] = g; }
-                if (check) {
-                    if (wk < thr * E[k]) cl = 1;
-                    chk = fma(q[k], 0.0, chk);
-                    chk = fma(wk, 0.0, chk);
-                    chk = fma(E[k], 0.0, chk);
-                }
-                F[k * RS + col] = make_double2(f1, g);
-                if (!FULL) {
-                    if (j >= N - 3 && j <= N - 2)    // f1 odd, g even about pi/2
-                        F[slot(2 * (N - 1) - j)] = make_double2(-f1, g);
-                }
-            }
-        }
-        if (tid == 0) {                              // f1 even, g odd about x = 0
-            F[(P - 1) * RS] = make_double2(f1a[1], -ga[1]);
-            F[(P - 2) * RS] = make_double2(f1a[2], -ga[2]);
-        }
-        if (FULL) {
-            if (tid == NL - 1) {
-                // f1_{N-1} = 0; g_{N-1} is the even 6th-order extrapolation of
-                // the finite limit at pi/2; then the ghosts N, N+1
-                F[0 * RS + NL + 1] = make_double2(0.0, (15.0 * gl[0] - 6.0 * gl[1] + gl[2]) / 10.0);
-                F[1 * RS + NL + 1] = make_double2(-fl[0], gl[0]);
-                F[2 * RS + NL + 1] = make_double2(-fl[1], gl[1]);
-            }
-        } else if (has_nm2) {
-            F[slot(N - 1)] = make_double2(0.0, 0.0);  // g_{N-1} set by the readers
-        }
-        if (check) {
-            if (1.0 < thr) cl = 1;
-            if (!isfinite(dN) || !isfinite(chk)) cl |= 2;
-            const int wcol = __any(cl & 1) ? 1 : 0;
-            const int wnf = __any(cl & 2) ? 2 : 0;
-            if (lane == 0) red[2 * W + wv] = (double)(wcol | wnf);
-        }
-        if constexpr (KEEP) {
-            // after the flux loop, so that its table loads do not wait for
-            // these stores (vector loads and stores retire in issue order)
-            const auto es = stage_rec<P, NL>(ES, tid);
-#pragma unroll
-            for (int k = 0; k < P; ++k) es.st(ks, k, v0[k], v1[k], E[k], S[k]);
-        }
-        __syncthreads();  // B3
-        if (check) {
-            int fl_ = 0;
-#pragma unroll
-            for (int v = 0; v < W; ++v) fl_ |= (int)red[2 * W + v];
-            if (fl_) return fl_;
-        }
-
-        double2 fw[P + 4];                           // points i0-2 .. i0+P+1
-#pragma unroll
-        for (int t = 0; t < P + 4; ++t) {
-            const int tt = t - 2;
-            if (tt < 0) fw[t] = F[(P + tt) * RS + col - 1];
-            else if (tt < P) fw[t] = F[tt * RS + col];
-            else fw[t] = F[(tt - P) * RS + col + 1];
-        }
-        if (!FULL && near_end) {
-            const int tN = (N - 1) - (i0 - 2);
-            if (tN >= 0 && tN < P + 4) {
-                const double gext = (15.0 * F[slot(N - 2)].y - 6.0 * F[slot(N - 3)].y + F[slot(N - 4)].y) / 10.0;
-#pragma unroll
-                for (int t = 0; t < P + 4; ++t)
-                    if (t == tN) fw[t].y = gext;
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < P; ++k) {
-            // interior formula everywhere (cot^2 x is 0 at x = 0 in the table);
-            // the origin row and points past N-2 are fixed up below
-            const double Df1 = (fw[k].x - 8.0 * fw[k + 1].x + 8.0 * fw[k + 3].x - fw[k + 4].x) * i12h;
-            const double Dg = (fw[k].y - 8.0 * fw[k + 1].y + 8.0 * fw[k + 3].y - fw[k + 4].y) * i12h;
-            r0[k] = Df1 + ko0[k];
-            r1[k] = tab(tb, 2, k) * Dg + ko1[k];
-            if (k == 0 && tid == 0) {
-                // Phi_0 = 0; lim tan^-2 (tan^2 f2)' = 3 f2'(0) with f2 odd about x = 0
-                r0[k] = 0.0;
-                r1[k] = 3.0 * ((16.0 * f2_1 - 2.0 * f2_2) * i12h) + ko1[k];
-            }
-            if (!own(k)) {
-                r0[k] = 0.0;
-                r1[k] = 0.0;
-            }
-        }
-        return 0;
-    }
-
-    // rhs on the edge path.  No barrier before the scans: the stage input is in
+    // Sums of two products are written with fma, so that the kernels that share this
+    // code (the recompute of a segment for the adjoint among them) round alike.
+    // No barrier before the scans: the stage input is in
     // registers and its edges were published before the first scan barrier.
     // The stage-input and flux slots (XU, XF) are double-buffered by stage, so
     // their last readers (after B3) never meet the next stage's writers even
     // with the metric frozen, when B3 is a stage's only barrier; the scan slots
     // (XP, XS) are written before B1 / B2 and read after them, with B3 between
     // a stage's reads and the next stage's writes.
-    // Barriers one call of rhs_edge passes (EVA off): B1, B2 and B3, or B3
-    // alone with the metric frozen.
-    static __device__ __forceinline__ int edge_barriers(bool frozen) { return frozen ? 1 : 3; }
-
-    template <bool KEEP, bool EVA>
-    __device__ __forceinline__ int rhs_edge(bool check, bool frozen, const double* v0, const double* v1, double* r0,
-                                            double* r1, ADSCL_GLOBAL double* ES, int ks, double* av, double* wout,
-                                            bool reint)
+    template <bool KEEP = false, bool EVA = false>
+    __device__ __forceinline__ int rhs(bool check, bool frozen, const double* v0, const double* v1, double* r0,
+                                       double* r1, ADSCL_GLOBAL double* ES = nullptr, int ks = 0,
+                                       double* av = nullptr, double* wout = nullptr, bool reint = false)
     {
         const auto tb = tables();
         double q[P];
 #pragma unroll
-        for (int k = 0; k < P; ++k) q[k] = v0[k] * v0[k] + v1[k] * v1[k];
+        for (int k = 0; k < P; ++k) q[k] = fma(v0[k], v0[k], v1[k] * v1[k]);
         double dl[P], E[P], S[P];
         double dN = 0.0, tot2 = 0.0;
         if (!frozen) {
@@ -890,6 +654,7 @@ struct Stage {
 #pragma unroll
             for (int k = 0; k < P; ++k) { dl[k] = 0.0; E[k] = 1.0; S[k] = 0.0; }
         }
+        double wr[KEEP ? P : 1];  // w for the record
         double ff[P], fg[P], chk = 0.0, f2_1 = 0.0, f2_2 = 0.0;
         int cl = 0;
 #pragma unroll
@@ -903,6 +668,7 @@ struct Stage {
             } else {
                 wk = E[k] - c3s * S[k];
             }
+            if constexpr (KEEP) wr[k] = wk;
             const double f2 = wk * v0[k];
             ff[k] = wk * v1[k];
             fg[k] = tab(tb, 1, k) * f2;
@@ -932,7 +698,7 @@ struct Stage {
             }
             if (FULL && tid == NL - 1) {
                 // f1_{N-1} = 0, g_{N-1} the even 6th-order extrapolation; ghost N
-                XFb[(W + 1) * 4] = make_double2(0.0, (15.0 * fg[P - 1] - 6.0 * fg[P - 2] + fg[P - 3]) / 10.0);
+                XFb[(W + 1) * 4] = make_double2(0.0, (fma(15.0, fg[P - 1], -6.0 * fg[P - 2]) + fg[P - 3]) / 10.0);
                 XFb[(W + 1) * 4 + 1] = make_double2(-ff[P - 1], fg[P - 1]);
             }
             if constexpr (RAG) {
@@ -952,9 +718,9 @@ struct Stage {
         if constexpr (KEEP) {
             // after the flux loop, so that its table loads do not wait for
             // these stores (vector loads and stores retire in issue order)
-            const auto es = stage_rec<P, NL>(ES, tid);
+            const auto es = stage_rec<P, NL>(ES + (size_t)ks * 4 * P * NL, tid);
 #pragma unroll
-            for (int k = 0; k < P; ++k) es.st(ks, k, v0[k], v1[k], E[k], S[k]);
+            for (int k = 0; k < P; ++k) es.st(k, v0[k], v1[k], E[k], wr[k]);
         }
         __syncthreads();  // B3
         if (check) {
@@ -1002,15 +768,15 @@ struct Stage {
         for (int k = 0; k < P; ++k) fw[2 + k] = make_double2(ff[k], fg[k]);
 #pragma unroll
         for (int k = 0; k < P; ++k) {
-            const double Df1 = (fw[k].x - 8.0 * fw[k + 1].x + 8.0 * fw[k + 3].x - fw[k + 4].x) * i12h;
+            const double Df1 = fw[k].x - 8.0 * fw[k + 1].x + 8.0 * fw[k + 3].x - fw[k + 4].x;
             const double Dg = (fw[k].y - 8.0 * fw[k + 1].y + 8.0 * fw[k + 3].y - fw[k + 4].y) * i12h;
-            r0[k] = Df1 + ko0[k];
-            r1[k] = tab(tb, 2, k) * Dg + ko1[k];
+            r0[k] = fma(Df1, i12h, ko0[k]);
+            r1[k] = fma(tab(tb, 2, k), Dg, ko1[k]);
         }
         if (tid == 0) {
             // Phi_0 = 0; lim tan^-2 (tan^2 f2)' = 3 f2'(0) with f2 odd about x = 0
             r0[0] = 0.0;
-            r1[0] = 3.0 * ((16.0 * f2_1 - 2.0 * f2_2) * i12h) + ko1[0];
+            r1[0] = fma(3.0, (16.0 * f2_1 - 2.0 * f2_2) * i12h, ko1[0]);
         }
         if constexpr (RAG) end_terms(r0, r1);
         return 0;

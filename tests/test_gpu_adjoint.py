@@ -302,3 +302,23 @@ def test_adjoint_strong_field_suffix_sums(N, ns):
     assert v[0] == int(ref["valid"]) == 1
     e = relmax(g[0], ref["grad"])
     assert e <= GTOL, "N=%d, %d steps: gradient error %.3e" % (N, ns, e)
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("P,W,Ns", [(4, 1, [65, 67, 69, 71]), (4, 2, [255, 257, 259, 261]),
+                                    (8, 1, [65, 67, 69, 71, 73, 75, 77, 79]), (16, 1, [17, 33, 35, 63, 65])])
+def test_adjoint_end_at_every_place_of_a_lane(monkeypatch, P, W, Ns, mode):
+    """Ragged grids whose last points lie at every odd place of a lane, and on either side
+    of a wavefront's end (data and window of test_adjoint_ragged_batch_matches_oracle,
+    whose tolerance holds for the same reason)."""
+    set_mode(monkeypatch, mode)
+    monkeypatch.setenv("ADSCL_TUNE", ",".join("%d:%dx%d" % (N, P, W) for N in Ns))
+    n = len(Ns)
+    eps = np.linspace(0.3, 1.0, n)
+    c = coeffs(11, n, 8)
+    print("adjoint ends", P, W, Ns, mode, flush=True)
+    _, L, g, v = run_gpu(np.array(Ns, np.int32), eps, c, 4, 0.2, 7)
+    assert v.tolist() == [1] * n
+    for b in range(n):
+        ref = O.objective(Ns[b], float(eps[b]), c[b], T=0.2, J=4, K=7)
+        assert relmax(g[b], ref["grad"]) <= GTOL, Ns[b]
