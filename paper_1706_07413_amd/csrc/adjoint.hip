@@ -654,12 +654,11 @@ __global__ void adj_prepare_kernel(int n_inst, const InstConst* ic, const InstSt
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= n_inst) return;
     const int64_t nf = ic[b].n_final;
-    const int64_t nseg = (nf + K - 1) / K;
-    const int64_t s = nseg - 1 - r;
-    const bool act = st[b].state == ST_DONE && s >= 0;
+    const int64_t n1 = nf - r * K;
+    const bool act = st[b].state == ST_DONE && n1 > 0;
     AdjSeg g;
-    g.n0 = act ? s * K : 0;
-    g.n1 = act ? ((s + 1) * K < nf ? (s + 1) * K : nf) : 0;
+    g.n0 = act && n1 > K ? n1 - K : 0;
+    g.n1 = act ? n1 : 0;
     g.active = act ? 1 : 0;
     g.pad = 0;
     sg[b] = g;

@@ -409,12 +409,15 @@ EvolveArgs evolve_args(adscl_ctx* c, int32_t snap_every)
     a.ckpt_every = 0;
     a.src_every = 1;
     a.a_reint = c->a_reint;
+    a.tail = 0;
     return a;
 }
 
 // One segment of the fused kernel over all classes: every instance advances to
 // its target step, or to its next multiple of snap_every when that is > 0.
-int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true)
+// `then`: a second launch of each class right after its first (the adjoint's forward
+// run, whose last segment is recorded; one workgroup per instance only).
+int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const EvolveArgs* then = nullptr)
 {
     for (BigGroup& g : c->big_groups) {
         BigArgs x;
@@ -437,7 +440,7 @@ int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true)
             }
         }
     }
-    const bool pairs = base.keep == nullptr;  // the pair kernel writes no stage records
+    const bool pairs = base.keep == nullptr && !then;  // the pair kernel writes no stage records
     return run_classes(c, [&](LaunchClass& lc, hipStream_t s) -> hipError_t {
         if (pairs && lc.host >= 0) {  // runs in its host class's launch
             lc.timed = false;
@@ -456,6 +459,11 @@ int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true)
                           : launch_evolve(lc.cfg, lc.full, (int)lc.inst.size(), a, s);
         }
         if (e != hipSuccess) return e;
+        if (then) {
+            EvolveArgs t = *then;
+            t.order = lc.d_order;
+            if ((e = launch_evolve(lc.cfg, lc.full, (int)lc.inst.size(), t, s)) != hipSuccess) return e;
+        }
         if (timing && lc.t1) {
             if ((e = hipEventRecord(lc.t1, s)) != hipSuccess) return e;
             lc.timed = true;
@@ -594,8 +602,8 @@ int after_init(adscl_ctx* c)
 // Device buffers and step counts of one adjoint configuration (T, K, J).
 struct AdjPlan {
     int J = 0;
-    int64_t K = 0;
-    int64_t max_seg = 0;
+    int64_t K = 0;        // steps of a segment
+    int64_t max_seg = 0;  // segments of the longest run
     double *ub = nullptr, *u0 = nullptr, *dummy = nullptr;
     double *E0 = nullptr, *a0 = nullptr, *b0 = nullptr, *ET = nullptr, *aT = nullptr, *bT = nullptr;
     double** d_ckp = nullptr;
@@ -614,35 +622,73 @@ int adj_plan(adscl_ctx* c, double T, int64_t K, int J, AdjPlan& pl)
     const int n = c->n_inst;
     int rc;
     std::vector<int64_t> nf(n), ck_off(n + 1), seg_off(n + 1), stg_off(n + 1), keep_off(n + 1);
+    int64_t max_nf = 0;
+    for (int b = 0; b < n; ++b) {
+        const double r = T / c->h_ic[b].dt - 1e-9;
+        nf[b] = (r <= 0.0) ? 0 : (int64_t)std::ceil(r);
+        max_nf = std::max(max_nf, nf[b]);
+    }
+    // bytes of the stage records of segments of k steps
+    auto record_bytes = [&](int64_t k) {
+        double s = 0.0;
+        for (int b = 0; b < n; ++b)
+            s += 8.0 * (double)std::min<int64_t>(k, nf[b]) * (double)stage_record_len(c->tables[c->N[b]].cfg);
+        return s;
+    };
+    // Keep each segment's stage records from the forward run or recompute (the reverse
+    // kernel then reads the stages instead of recomputing them) when the
+    // records take at most a quarter of the device memory; ADSCL_ADJOINT_RECOMPUTE
+    // set to a value other than 0 always recomputes.
+    size_t free_b = 0, total_b = 0;
+    HIP_TRY(c, hipMemGetInfo(&free_b, &total_b));
+    auto env_set = [](const char* name) {
+        const char* v = std::getenv(name);
+        return v && v[0] && std::strcmp(v, "0") != 0;
+    };
+    const bool force = env_set("ADSCL_ADJOINT_RECOMPUTE");
+    pl.stored = !force && record_bytes(K) <= (double)(total_b / 4);
+    // Segments longer than asked for where their records are small: the forward run
+    // records its last segment itself, so what fits in one is computed once instead of
+    // twice (N = 4097, 1043 steps in segments of 512: 50 ms a gradient with the last
+    // segment recorded, 43 with all of them).  Within a thirty-second of the device
+    // memory, and within half of what is free beside the records held already.
+    // ADSCL_ADJOINT_SEGMENTS set to a value other than 0 takes them as asked for.
+    const int64_t asked = K;
+    if (pl.stored && !env_set("ADSCL_ADJOINT_SEGMENTS")) {
+        const double room = std::min((double)(total_b / 32), 0.5 * (double)free_b + (double)c->bufs["keep"].second);
+        int64_t lo = K, hi = max_nf;  // record_bytes does not fall
+        while (lo < hi) {
+            const int64_t mid = hi - (hi - lo) / 2;
+            if (record_bytes(mid) <= room) lo = mid;
+            else hi = mid - 1;
+        }
+        K = std::min<int64_t>(lo, INT32_MAX);
+    }
+    void* keep = nullptr;
+    if (pl.stored) {
+        rc = buffer(c, "keep", (size_t)record_bytes(K), &keep);
+        if (rc == ADSCL_ENOMEM && K > asked) {
+            (void)hipGetLastError();
+            K = asked;
+            rc = buffer(c, "keep", (size_t)record_bytes(K), &keep);
+        }
+        if (rc) return rc;
+    }
     pl.J = J;
     pl.K = K;
     pl.max_seg = 0;
     for (int b = 0; b < n; ++b) {
-        const double r = T / c->h_ic[b].dt - 1e-9;
-        nf[b] = (r <= 0.0) ? 0 : (int64_t)std::ceil(r);
         const NTables& t = c->tables[c->N[b]];
-        ck_off[b + 1] = ck_off[b] + (nf[b] / K + 1) * 2 * (int64_t)c->N[b];
+        ck_off[b + 1] = ck_off[b] + ((nf[b] + K - 1) / K + 1) * 2 * (int64_t)c->N[b];
         seg_off[b + 1] = seg_off[b] + (std::min<int64_t>(K, nf[b]) + 1) * 2 * (int64_t)c->N[b];
         stg_off[b + 1] = stg_off[b] + (int64_t)adjoint_scratch_len(t.cfg);
         keep_off[b + 1] = keep_off[b] + std::min<int64_t>(K, nf[b]) * (int64_t)stage_record_len(t.cfg);
         pl.max_seg = std::max<int64_t>(pl.max_seg, (nf[b] + K - 1) / K);
     }
-    // Keep each segment's stage record from the forward recompute (the reverse
-    // kernel then reads the stages instead of recomputing them) when the
-    // records take at most a quarter of the device memory; ADSCL_ADJOINT_RECOMPUTE
-    // set to a value other than 0 always recomputes.
-    {
-        size_t free_b = 0, total_b = 0;
-        HIP_TRY(c, hipMemGetInfo(&free_b, &total_b));
-        const char* env = std::getenv("ADSCL_ADJOINT_RECOMPUTE");
-        const bool force = env && env[0] && std::strcmp(env, "0") != 0;
-        pl.stored = !force && sizeof(double) * (size_t)keep_off[n] <= total_b / 4;
-    }
-    void *ck, *seg, *stg, *keep = nullptr, *ub, *u0, *dummy, *spec, *ptrs, *rst, *sgs;
+    void *ck, *seg, *stg, *ub, *u0, *dummy, *spec, *ptrs, *rst, *sgs;
     const size_t nJ = (size_t)n * J;
     if ((rc = buffer(c, "ckpt", sizeof(double) * ck_off[n], &ck))) return rc;
     if (pl.stored) {
-        if ((rc = buffer(c, "keep", sizeof(double) * keep_off[n], &keep))) return rc;
         seg_off.assign(n + 1, 0);  // no per-step states needed, nor scratch to recompute stages in
         stg_off.assign(n + 1, 0);
     }
@@ -684,8 +730,9 @@ int adj_plan(adscl_ctx* c, double T, int64_t K, int J, AdjPlan& pl)
 }
 
 // Device part: the whole gradient computation for data eps, c (device arrays)
-// -- initial data and its spectrum, the evolution with checkpoints, the final
-// spectrum, then the reverse sweep segment by segment and the initial map.
+// -- initial data and its spectrum, the evolution with checkpoints and its last segment
+// recorded, the final spectrum, then the reverse sweep segment by segment (each but the
+// last recomputed first) and the initial map.
 // Only kernel launches, event waits and device copies: no host
 // synchronisation and no memset, so that it can be captured into a graph.
 // Instances with active[b] == 0 (when active is given) are skipped.
@@ -708,7 +755,14 @@ int adj_enqueue(adscl_ctx* c, const AdjPlan& pl, const double* d_eps, const doub
         EvolveArgs a = evolve_args(c, 0);
         a.ckpt = pl.d_ckp;
         a.ckpt_every = (int32_t)pl.K;
-        if ((rc = run_evolve(c, a, timing))) return rc;
+        if (pl.stored) {  // the last segment is recorded on the way
+            EvolveArgs t = evolve_args(c, 0);
+            t.keep = pl.d_keepp;
+            a.tail = pl.K;
+            if ((rc = pl.max_seg > 1 ? run_evolve(c, a, timing, &t) : run_evolve(c, t, timing))) return rc;
+        } else if ((rc = run_evolve(c, a, timing))) {
+            return rc;
+        }
     }
     if ((rc = run_finalize(c, true, 0, 0, nullptr))) return rc;
     if ((rc = run_spectrum(c, s5, J, pl.ET, pl.aT, pl.bT))) return rc;
@@ -765,10 +819,12 @@ int adj_enqueue(adscl_ctx* c, const AdjPlan& pl, const double* d_eps, const doub
     for (int64_t r = 0; r < pl.max_seg; ++r) {
         HIP_TRY(c, launch_adj_prepare(n, c->d_ic, c->d_status, pl.K, r, pl.rst, pl.sgs, c->stream));
         rc = run_classes(c, [&](LaunchClass& lc, hipStream_t s) -> hipError_t {
-            EvolveArgs e = ra;
-            e.order = lc.d_order;
-            hipError_t err = launch_evolve(lc.cfg, lc.full, (int)lc.inst.size(), e, s);
-            if (err != hipSuccess) return err;
+            if (r > 0 || !pl.stored) {
+                EvolveArgs e = ra;
+                e.order = lc.d_order;
+                const hipError_t err = launch_evolve(lc.cfg, lc.full, (int)lc.inst.size(), e, s);
+                if (err != hipSuccess) return err;
+            }
             AdjointArgs g = aa;
             g.order = lc.d_order;
             return launch_adjoint(lc.cfg, lc.full, (int)lc.inst.size(), g, s);

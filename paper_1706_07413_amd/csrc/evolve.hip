@@ -42,11 +42,12 @@ struct Run {
     Stage<P, W, FULL, true> sg;
     double un0[P], un1[P], acc0[P], acc1[P], cv0[P], cv1[P];  // cv: the current stage input
     InstStatus st0;
-    int64_t off, n, seg_end;
+    int64_t off, n, seg_end, n_final;
     double dt;
     int stop_bits;
     bool frozen;
-    ADSCL_GLOBAL double* ck;    // checkpoints of the segment, or null
+    ADSCL_GLOBAL double* ck;    // the next checkpoint, or null
+    int64_t ck_next;            // and its step
     ADSCL_GLOBAL double* kp;    // KEEP: the segment's stage records
     ADSCL_GLOBAL double* krec;  // KEEP: the current step's record
 
@@ -57,6 +58,7 @@ struct Run {
         if (st0.state == ST_COLLAPSED || st0.state == ST_NONFINITE) return false;
         const InstConst ic = a.ic[b];
         off = ic.off;
+        n_final = ic.n_final;
         frozen = a.frozen != 0;
         sg.setup(lds, ic, a.tab[b], a.gauge, a.a_collapse, t);
         const int N = sg.N, i0 = sg.i0;
@@ -64,7 +66,8 @@ struct Run {
         const ADSCL_GLOBAL double* s0 = gmem(a.Phi + off);
         const ADSCL_GLOBAL double* s1 = gmem(a.Pi + off);
         if (a.src) {
-            s0 = gmem(a.src[b]) + (size_t)(st0.steps / a.src_every) * 2 * (size_t)N;
+            s0 = gmem(a.src[b])
+                 + (size_t)((st0.steps + segment_phase(ic.n_final, a.src_every)) / a.src_every) * 2 * (size_t)N;
             s1 = s0 + N;
         }
 #pragma unroll
@@ -89,7 +92,11 @@ struct Run {
             const int64_t nb = (n / a.snap_every + 1) * a.snap_every;
             if (nb < seg_end) seg_end = nb;
         }
-        // checkpoints of the segment: U^n for n - n_start a multiple of ckpt_every
+        if (a.tail > 0) {
+            const int64_t e = ic.n_final - a.tail;
+            seg_end = e < n ? n : (e < seg_end ? e : seg_end);
+        }
+        ck_next = n;
         ck = (a.ckpt && a.ckpt_every > 0) ? gmem(a.ckpt[b]) : nullptr;
         return true;
     }
@@ -132,10 +139,9 @@ struct Run {
     // Start of step n: the checkpoint due at n, the step's stage record.
     __device__ __forceinline__ void begin_step(const EvolveArgs& a)
     {
-        const int64_t r = n - st0.steps;
-        if (ck && r % a.ckpt_every == 0) {
+        if (ck && n == ck_next) {
             const int N = sg.N, i0 = sg.i0;
-            ADSCL_GLOBAL double* d = ck + (size_t)(r / a.ckpt_every) * 2 * (size_t)N;
+            ADSCL_GLOBAL double* d = ck;
 #pragma unroll
             for (int k = 0; k < P; ++k) {
                 if (sg.own(k)) {
@@ -147,6 +153,9 @@ struct Run {
                 d[N - 1] = 0.0;
                 d[2 * N - 1] = 0.0;
             }
+            ck += 2 * (size_t)N;
+            ck_next += a.ckpt_every;
+            if (n == st0.steps) ck_next -= segment_phase(n_final, a.ckpt_every);
         }
         if (KEEP) krec = kp + (size_t)(n - st0.steps) * kRec;
     }

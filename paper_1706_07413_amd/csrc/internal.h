@@ -46,15 +46,15 @@ struct EvolveArgs {
     const int32_t* order;   // instance index per workgroup of this launch
     const double* const* tab;  // per instance: lane-interleaved tables of its class
     InstStatus* status;     // [n_inst]
-    // optional: per instance, stored states ([slot][2][N]: Phi then Pi, one
-    // every src_every steps) to start from, slot = n_start / src_every,
-    // instead of (Phi, Pi); and where to store the state every ckpt_every steps
-    // of the segment ([slot][2][N], slot = (n - n_start) / ckpt_every)
+    // optional: per instance, stored states ([slot][2][N]: Phi then Pi) to start from
+    // instead of (Phi, Pi), stored by a run from step 0 with ckpt_every = src_every; and
+    // where to store the state: at the launch's first step (slot 0) and from there at
+    // every step that lies a multiple of ckpt_every before n_final (the next slots)
     const double* const* src;
     double* const* ckpt;
-    // optional (the adjoint's segment recompute): per instance, the stage record
-    // of every step of the segment, [n - n_start][4 stages][P][64 W][4]: each RK
-    // stage's input (Phi, Pi), e^-delta and S (StageRec in stage.h)
+    // optional (for the adjoint): per instance, the stage record
+    // of every step of the launch, [n - n_start][4 stages]: each RK stage's
+    // input (Phi, Pi), e^-delta and A e^-delta (StageRec in stage.h)
     double* const* keep;
     int64_t total;
     double a_collapse;
@@ -64,7 +64,12 @@ struct EvolveArgs {
     int32_t ckpt_every;
     int32_t src_every;
     int32_t a_reint;        // A evolved by Eq. (4), re-integrated every a_reint steps (0: solved)
+    int64_t tail;           // fused RK4 kernel: stop this many steps before n_final (0: at the target)
 };
+
+// Steps before the first of the steps that lie a multiple of K before n_final, less K:
+// segments of K steps are counted from the end of a run, and the first may be shorter.
+__host__ __device__ inline int64_t segment_phase(int64_t n_final, int64_t K) { return (K - n_final % K) % K; }
 
 // A kernel configuration: P grid points per lane, W wavefronts per instance.
 struct ClassCfg {
@@ -254,8 +259,8 @@ size_t stage_record_len(ClassCfg c);
 hipError_t prepare_adjoint(ClassCfg c, size_t max_lds);
 hipError_t launch_adjoint(ClassCfg c, bool full, int n_blocks, const AdjointArgs& a, hipStream_t s);
 hipError_t launch_endpoint(ClassCfg c, bool full, int n_blocks, const EndArgs& a, hipStream_t s);
-// Segment r (counted from the end) of every instance that is DONE: recompute
-// status rst (steps n0, target n1; others COLLAPSED so the kernels skip them)
+// Segment r of K steps (counted from the end; the first of a run may be shorter) of
+// every instance that is DONE: recompute status rst (steps n0, target n1; others COLLAPSED so the kernels skip them)
 // and the reverse range sg.
 hipError_t launch_adj_prepare(int n_inst, const InstConst* ic, const InstStatus* st, int64_t K, int64_t r,
                               InstStatus* rst, AdjSeg* sg, hipStream_t s);

@@ -322,3 +322,24 @@ def test_adjoint_end_at_every_place_of_a_lane(monkeypatch, P, W, Ns, mode):
     for b in range(n):
         ref = O.objective(Ns[b], float(eps[b]), c[b], T=0.2, J=4, K=7)
         assert relmax(g[b], ref["grad"]) <= GTOL, Ns[b]
+
+
+@pytest.mark.parametrize("K", [1, 5, 24, 25, 26, 10 ** 6])
+def test_adjoint_segments_as_asked_or_longer_give_the_same_bits(monkeypatch, K):
+    """Segments of K steps with the last recorded by the forward run, against one segment
+    for the whole run: 25, 49 and 12 steps, so that K divides the runs, leaves a short
+    first segment, or exceeds some or all of them."""
+    Ns = np.array([65, 129, 33], np.int32)
+    eps = np.array([0.6, 0.4, 0.5])
+    c = coeffs(12, 3, 6)
+    print("adjoint segments", K, flush=True)
+    _, L1, g1, v1 = run_gpu(Ns, eps, c, 3, 0.15, K)
+    monkeypatch.setenv("ADSCL_ADJOINT_SEGMENTS", "1")
+    b, L2, g2, v2 = run_gpu(Ns, eps, c, 3, 0.15, K)
+    assert np.array_equal(L1, L2) and np.array_equal(g1, g2) and np.array_equal(v1, v2)
+    # the context is left where a plain run would have left it
+    st = {k: v.cpu().numpy() for k, v in b.get_state().items()}
+    b.init_modes(eps, c)
+    b.step(10 ** 6, 0.15)
+    for k, v in b.get_state().items():
+        assert np.array_equal(st[k], v.cpu().numpy()), k
