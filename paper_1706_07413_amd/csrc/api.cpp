@@ -31,10 +31,11 @@ struct LaunchClass {
     bool full;
     std::vector<int32_t> inst;
     int32_t* d_order = nullptr;
-    hipStream_t stream = nullptr;
+    hipStream_t stream = nullptr;  // null: the context's stream
     hipEvent_t done = nullptr;
     hipEvent_t t0 = nullptr, t1 = nullptr;  // timing (ADSCL_TIME_KERNELS)
     bool timed = false;
+    int fits = 0;  // one-workgroup instances the device holds at once
     // one large instance over `chunks` workgroups (0: one workgroup per instance)
     int chunks = 0;
     // forward pass only: the class whose instances this class's launch also
@@ -100,6 +101,8 @@ struct adscl_ctx {
     // adjoint working memory, kept for reuse by later calls
     std::map<std::string, std::pair<void*, size_t>> bufs;
     hipEvent_t fork = nullptr;  // start of a multi-class launch, recorded on `stream`
+    bool paired = false;        // some class runs another's instances (pair launches)
+    double over = 0.0;          // one-workgroup instances, as shares of what the device holds at once
     int n_big = 0;              // classes holding one large (multi-workgroup) instance
     std::vector<BigGroup> big_groups;  // their launches
     // spectrum rows for states laid out as [slot][5][total], and their tiles of one
@@ -360,26 +363,31 @@ int buffer(adscl_ctx* c, const char* name, size_t bytes, void** out)
     return ADSCL_OK;
 }
 
-// One launch per class, the classes concurrently (one stream per class, forked
-// from and joined back into the context stream).  `launch(lc, stream)` enqueues
+// One launch per class, the classes concurrently (on streams forked from and joined
+// back into the context stream).  `launch(lc, stream)` enqueues
 // the class's work.
+template <class F, class Sel>
+int run_classes(adscl_ctx* c, F&& launch, Sel&& selected)
+{
+    hipEvent_t fork = c->fork;
+    if (fork) HIP_TRY(c, hipEventRecord(fork, c->stream));
+    for (LaunchClass& lc : c->classes) {
+        if (lc.chunks > 0 || !selected(lc)) continue;
+        hipStream_t s = lc.stream ? lc.stream : c->stream;
+        if (s != c->stream) HIP_TRY(c, hipStreamWaitEvent(s, fork, 0));
+        HIP_TRY(c, launch(lc, s));
+        if (s != c->stream) HIP_TRY(c, hipEventRecord(lc.done, s));
+    }
+    // joined only now: a class on the context's stream waits for none of the others
+    for (LaunchClass& lc : c->classes)
+        if (lc.chunks == 0 && selected(lc) && lc.stream) HIP_TRY(c, hipStreamWaitEvent(c->stream, lc.done, 0));
+    return ADSCL_OK;
+}
+
 template <class F>
 int run_classes(adscl_ctx* c, F&& launch)
 {
-    hipEvent_t fork = c->fork;
-    const bool multi = c->classes.size() - c->n_big > 1;
-    if (multi) HIP_TRY(c, hipEventRecord(fork, c->stream));
-    for (LaunchClass& lc : c->classes) {
-        if (lc.chunks > 0) continue;
-        hipStream_t s = multi ? lc.stream : c->stream;
-        if (s != c->stream) HIP_TRY(c, hipStreamWaitEvent(s, fork, 0));
-        HIP_TRY(c, launch(lc, s));
-        if (s != c->stream) {
-            HIP_TRY(c, hipEventRecord(lc.done, s));
-            HIP_TRY(c, hipStreamWaitEvent(c->stream, lc.done, 0));
-        }
-    }
-    return ADSCL_OK;
+    return run_classes(c, std::forward<F>(launch), [](const LaunchClass&) { return true; });
 }
 
 // Whether the context uses a scheme option other than classical RK4 with A
@@ -409,6 +417,10 @@ EvolveArgs evolve_args(adscl_ctx* c, int32_t snap_every)
     a.ckpt_every = 0;
     a.src_every = 1;
     a.a_reint = c->a_reint;
+    a.slice = 0;
+    a.order_first = 0;
+    a.order_n = 0;
+    a.pad = 0;
     a.tail = 0;
     return a;
 }
@@ -417,7 +429,8 @@ EvolveArgs evolve_args(adscl_ctx* c, int32_t snap_every)
 // its target step, or to its next multiple of snap_every when that is > 0.
 // `then`: a second launch of each class right after its first (the adjoint's forward
 // run, whose last segment is recorded; one workgroup per instance only).
-int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const EvolveArgs* then = nullptr)
+int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const EvolveArgs* then = nullptr,
+               int64_t steps = 0)
 {
     for (BigGroup& g : c->big_groups) {
         BigArgs x;
@@ -441,7 +454,25 @@ int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const E
         }
     }
     const bool pairs = base.keep == nullptr && !then;  // the pair kernel writes no stage records
-    return run_classes(c, [&](LaunchClass& lc, hipStream_t s) -> hipError_t {
+    // More instances than the compute units hold at once run in slices, some steps at a
+    // time, so that what a class leaves idle at its end is a slice long and not a whole
+    // run.  A class that fills the device by itself runs alone first, as many
+    // workgroups at a time as fit, its instances in turn (a compute unit that holds
+    // workgroups of several classes holds fewer wavefronts); the others then run side
+    // by side.
+    // Measured, ms, against every class in one launch on a stream of its own: 1024
+    // instances of 1025, 2049 and 4097 points, 512 steps, 26.4 -> 21.1; 250 + 324 + 349 of
+    // 4097, 2049 and 1025, 256 steps, 11.3 -> 8.9; 300 of 4097, 8.5 -> 5.3; 600 of 2049,
+    // 6.5 -> 4.9 (4 to 32 slices are alike).
+    int n_slices = 1;
+    if (steps > 0 && steps < INT32_MAX && c->over > 1.0 && pairs && !c->paired && !base.ckpt && !scheme(c))
+        n_slices = (int)std::max<int64_t>(1, std::min<int64_t>(8, steps / 16));
+    auto share = [](const LaunchClass& lc) { return (double)lc.inst.size() / lc.fits; };
+    auto alone = [&](const LaunchClass& lc) { return n_slices > 1 && lc.chunks == 0 && share(lc) >= 0.8; };
+    double rest = c->over;
+    for (const LaunchClass& lc : c->classes)
+        if (alone(lc)) rest -= share(lc);
+    auto launch = [&](LaunchClass& lc, hipStream_t s) -> hipError_t {
         if (pairs && lc.host >= 0) {  // runs in its host class's launch
             lc.timed = false;
             return hipSuccess;
@@ -450,29 +481,51 @@ int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const E
         a.order = lc.d_order;
         hipError_t e = hipSuccess;
         if (timing && lc.t0 && (e = hipEventRecord(lc.t0, s)) != hipSuccess) return e;
+        const int n = (int)lc.inst.size();
         if (pairs && lc.pair >= 0) {
             a.order = lc.d_order_pair;
-            const int ns = (int)lc.inst.size();
-            e = launch_evolve_pair(lc.cfg, ns, ns + (int)c->classes[lc.pair].inst.size(), a, s);
+            e = launch_evolve_pair(lc.cfg, n, n + (int)c->classes[lc.pair].inst.size(), a, s);
+        } else if (scheme(c)) {
+            e = launch_evolve_scheme(lc.cfg, c->rk, c->a_reint > 0, lc.full, n, a, s);
+        } else if (n_slices > 1 && (alone(lc) || rest > 1.0)) {
+            // launch k takes the instances from k * blocks on, counted round; each has
+            // n_slices turns
+            const int blocks = alone(lc) ? std::min(n, lc.fits) : n;
+            const int launches = (int)(((int64_t)n * n_slices + blocks - 1) / blocks);
+            a.slice = (int32_t)((steps + n_slices - 1) / n_slices);
+            a.order_n = n;
+            for (int k = 0; k < launches && e == hipSuccess; ++k) {
+                a.order_first = (int32_t)((int64_t)k * blocks % n);
+                e = launch_evolve(lc.cfg, lc.full, blocks, a, s);
+            }
         } else {
-            e = scheme(c) ? launch_evolve_scheme(lc.cfg, c->rk, c->a_reint > 0, lc.full, (int)lc.inst.size(), a, s)
-                          : launch_evolve(lc.cfg, lc.full, (int)lc.inst.size(), a, s);
+            e = launch_evolve(lc.cfg, lc.full, n, a, s);
         }
         if (e != hipSuccess) return e;
         if (then) {
             EvolveArgs t = *then;
             t.order = lc.d_order;
-            if ((e = launch_evolve(lc.cfg, lc.full, (int)lc.inst.size(), t, s)) != hipSuccess) return e;
+            if ((e = launch_evolve(lc.cfg, lc.full, n, t, s)) != hipSuccess) return e;
         }
         if (timing && lc.t1) {
             if ((e = hipEventRecord(lc.t1, s)) != hipSuccess) return e;
             lc.timed = true;
         }
         return hipSuccess;
-    });
+    };
+    for (LaunchClass& lc : c->classes)
+        if (alone(lc)) HIP_TRY(c, launch(lc, c->stream));
+    return run_classes(c, launch, [&](const LaunchClass& lc) { return !alone(lc); });
 }
 
-int run_evolve(adscl_ctx* c, int32_t snap_every) { return run_evolve(c, evolve_args(c, snap_every)); }
+// The same, at most `steps` steps.
+int run_evolve(adscl_ctx* c, int32_t snap_every, int64_t steps)
+{
+    int64_t most = 0;
+    for (const InstConst& k : c->h_ic) most = std::max(most, k.n_final);
+    if (snap_every > 0) most = std::min<int64_t>(most, snap_every);
+    return run_evolve(c, evolve_args(c, snap_every), true, nullptr, std::min(most, steps));
+}
 
 int run_finalize(adscl_ctx* c, bool final, int32_t snap_every, int32_t n_slots, double* snaps)
 {
@@ -543,11 +596,11 @@ int run_call(adscl_ctx* c, int64_t max_steps, double t_end, int32_t snap_every, 
             for (const InstStatus& s : st)
                 if ((s.state == ST_RUNNING || s.state == ST_DONE) && s.steps < s.target) more = true;
             if (!more) break;
-            if ((rc = run_evolve(c, snap_every))) return rc;
+            if ((rc = run_evolve(c, snap_every, max_steps))) return rc;
             if ((rc = run_finalize(c, false, snap_every, n_slots, snaps))) return rc;
         }
     } else {
-        if ((rc = run_evolve(c, 0))) return rc;
+        if ((rc = run_evolve(c, 0, max_steps))) return rc;
     }
     return run_finalize(c, true, 0, 0, nullptr);
 }
@@ -1115,10 +1168,6 @@ int adscl_create(const adscl_config* cfg, void* hip_stream, adscl_ctx** out)
         std::stable_sort(lc.inst.begin(), lc.inst.end(), [&](int x, int y) { return c->N[x] > c->N[y]; });
         TRY_C(hipMalloc((void**)&lc.d_order, lc.inst.size() * sizeof(int32_t)));
         TRY_C(hipMemcpy(lc.d_order, lc.inst.data(), lc.inst.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-        if (c->classes.size() > 1 && lc.chunks == 0) {
-            TRY_C(hipStreamCreateWithFlags(&lc.stream, hipStreamNonBlocking));
-            TRY_C(hipEventCreateWithFlags(&lc.done, hipEventDisableTiming));
-        }
         if (c->flags & ADSCL_TIME_KERNELS) {
             TRY_C(hipEventCreate(&lc.t0));
             TRY_C(hipEventCreate(&lc.t1));
@@ -1135,8 +1184,28 @@ int adscl_create(const adscl_config* cfg, void* hip_stream, adscl_ctx** out)
         if ((x.chunks > 0) != (y.chunks > 0)) return y.chunks > 0;
         return 64 * x.cfg.W * x.cfg.P > 64 * y.cfg.W * y.cfg.P;
     });
+    // each class on a stream of its own, where there are several; the first class's is
+    // created last, since a process has few hardware queues and run_evolve often runs
+    // that class on the context's stream
+    for (size_t k = 1; k <= c->classes.size() && c->classes.size() > 1; ++k) {
+        LaunchClass& lc = c->classes[k % c->classes.size()];
+        if (lc.chunks > 0) continue;
+        TRY_C(hipStreamCreateWithFlags(&lc.stream, hipStreamNonBlocking));
+        TRY_C(hipEventCreateWithFlags(&lc.done, hipEventDisableTiming));
+    }
     c->n_big = 0;
     for (const LaunchClass& lc : c->classes) c->n_big += lc.chunks > 0;
+    if (!scheme(c)) {
+        int cus = 0;
+        TRY_C(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
+        for (LaunchClass& lc : c->classes) {
+            if (lc.chunks > 0) continue;
+            int per_cu = 0;
+            TRY_C(evolve_per_cu(lc.cfg, lc.full, &per_cu));
+            lc.fits = std::max(1, per_cu * cus);
+            c->over += (double)lc.inst.size() / lc.fits;
+        }
+    }
     // Pair launches (plain RK4 only; after the sort, which fixes the class
     // indices that `pair` and `host` hold): a full (P, W) class also runs a full
     // (P, W/2) class's instances two per workgroup in its own launch, after its
@@ -1158,6 +1227,7 @@ int adscl_create(const adscl_config* cfg, void* hip_stream, adscl_ctx** out)
                 ord.insert(ord.end(), Y.inst.begin(), Y.inst.end());
                 TRY_C(hipMalloc((void**)&X.d_order_pair, ord.size() * sizeof(int32_t)));
                 TRY_C(hipMemcpy(X.d_order_pair, ord.data(), ord.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+                c->paired = true;
                 X.pair = y;
                 Y.host = x;
                 break;

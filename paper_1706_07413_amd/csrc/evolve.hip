@@ -92,6 +92,7 @@ struct Run {
             const int64_t nb = (n / a.snap_every + 1) * a.snap_every;
             if (nb < seg_end) seg_end = nb;
         }
+        if (a.slice > 0 && n + a.slice < seg_end) seg_end = n + a.slice;
         if (a.tail > 0) {
             const int64_t e = ic.n_final - a.tail;
             seg_end = e < n ? n : (e < seg_end ? e : seg_end);
@@ -205,7 +206,12 @@ template <int P, int W, bool FULL, bool KEEP>
 __global__ void __launch_bounds__(64 * W) evolve_kernel(EvolveArgs a)
 {
     extern __shared__ double lds[];
-    evolve_one<P, W, FULL, KEEP>(a, a.order[blockIdx.x], lds);
+    int i = blockIdx.x;
+    if (a.order_n > 0) {
+        i += a.order_first;
+        if (i >= a.order_n) i -= a.order_n;
+    }
+    evolve_one<P, W, FULL, KEEP>(a, a.order[i], lds);
 }
 
 // LDS doubles of one half of a pair workgroup (even, so that the second half's
@@ -369,6 +375,19 @@ hipError_t launch_evolve(ClassCfg c, bool full, int n_blocks, const EvolveArgs& 
 {
 #define X(p, w) \
     if (c.P == p && c.W == w) return launch_t<p, w>(full, n_blocks, a, s);
+    ADSCL_CLASSES(X)
+#undef X
+    return hipErrorInvalidValue;
+}
+
+hipError_t evolve_per_cu(ClassCfg c, bool full, int* n)
+{
+#define X(p, w)                                                                                                    \
+    if (c.P == p && c.W == w)                                                                                      \
+        return full ? hipOccupancyMaxActiveBlocksPerMultiprocessor(n, evolve_kernel<p, w, true, false>, 64 * w,    \
+                                                                   lds_bytes_for<p, w, true>())                   \
+                    : hipOccupancyMaxActiveBlocksPerMultiprocessor(n, evolve_kernel<p, w, false, false>, 64 * w,   \
+                                                                   lds_bytes_for<p, w, false>());
     ADSCL_CLASSES(X)
 #undef X
     return hipErrorInvalidValue;

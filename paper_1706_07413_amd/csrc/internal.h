@@ -64,6 +64,10 @@ struct EvolveArgs {
     int32_t ckpt_every;
     int32_t src_every;
     int32_t a_reint;        // A evolved by Eq. (4), re-integrated every a_reint steps (0: solved)
+    int32_t slice;          // fused RK4 kernel: at most this many steps (0: no limit)
+    int32_t order_first;    // fused RK4 kernel: workgroup i runs instance order[(order_first + i) mod order_n]
+    int32_t order_n;        // (order_n = 0: order[i])
+    int32_t pad;
     int64_t tail;           // fused RK4 kernel: stop this many steps before n_final (0: at the target)
 };
 
@@ -90,6 +94,8 @@ size_t evolve_lds_bytes(ClassCfg c);
 hipError_t prepare_evolve(ClassCfg c, size_t max_lds);
 // full: every instance of the launch has N - 1 == 64 W P.
 hipError_t launch_evolve(ClassCfg c, bool full, int n_blocks, const EvolveArgs& a, hipStream_t s);
+// Workgroups of that kernel a compute unit holds at once.
+hipError_t evolve_per_cu(ClassCfg c, bool full, int* n);
 // Pair launch of a full (P, W) class: a.order[0, n_single) are its instances
 // (one workgroup each), a.order[n_single, n_inst) instances of a full
 // (P, W/2) class, two per workgroup, in the same launch.

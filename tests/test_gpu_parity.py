@@ -419,3 +419,27 @@ def test_ends_of_ragged_grids(rk, K, frozen):
         for f in ("Phi", "Pi") if frozen else FIELDS:
             assert_close(g[f][o:o + N], ref[f], "N=%d rk %d K %d %s" % (N, rk, K, f))
         o += N
+
+
+@pytest.mark.parametrize("Ns", [[2049] * 520 + [65], [65] * 1200 + [17] * 1200 + [33] * 1300, [1025] * 900 + [2049] * 300 + [513]])
+def test_more_instances_than_the_device_holds_run_in_turn(Ns):
+    """Batches past what the compute units hold run in slices, classes that fill the device
+    alone and in turn: an instance's bits are those of a run by itself, its steps the ones
+    asked for, also past a call whose steps the slices do not divide."""
+    Ns = np.array(Ns, np.int32)
+    n = len(Ns)
+    eps = np.linspace(0.5, 2.0, n)
+    sig = np.full(n, 0.2)
+    print("slices", n, flush=True)
+    b = adscl.Batch(Ns, a_collapse=0.0)
+    b.init_gaussian(eps, sig)
+    b.step(67, 1e9)
+    b.step(33, 1e9)
+    assert np.all(b.status()["steps"] == 100)
+    st = {k: v.cpu().numpy() for k, v in b.get_state().items()}
+    for i in (0, n // 3, n // 2, n - 2, n - 1):
+        a = adscl.Batch(Ns[i:i + 1], a_collapse=0.0)
+        a.init_gaussian(eps[i:i + 1], sig[i:i + 1])
+        a.step(100, 1e9)
+        for k, v in a.get_state().items():
+            assert np.array_equal(b.split(st[k])[i], v.cpu().numpy()), (i, k)
