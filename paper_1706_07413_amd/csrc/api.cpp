@@ -465,7 +465,11 @@ int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const E
     // 4097, 2049 and 1025, 256 steps, 11.3 -> 8.9; 300 of 4097, 8.5 -> 5.3; 600 of 2049,
     // 6.5 -> 4.9 (4 to 32 slices are alike).
     int n_slices = 1;
-    if (steps > 0 && steps < INT32_MAX && c->over > 1.0 && pairs && !c->paired && !base.ckpt && !scheme(c))
+    // Only where few instances stop on the way, in calls of at most a light crossing,
+    // t = pi/2, of the largest grid: a launch of a whole class hands the place of an
+    // instance that stops to the next at once, a slice does not.
+    const bool brief = (double)steps * c->cfl <= (double)(std::min<int64_t>(c->max_N, kMaxOneGroup) - 1);
+    if (steps > 0 && brief && c->over > 1.0 && pairs && !c->paired && !base.ckpt && !scheme(c))
         n_slices = (int)std::max<int64_t>(1, std::min<int64_t>(8, steps / 16));
     auto share = [](const LaunchClass& lc) { return (double)lc.inst.size() / lc.fits; };
     auto alone = [&](const LaunchClass& lc) { return n_slices > 1 && lc.chunks == 0 && share(lc) >= 0.8; };
