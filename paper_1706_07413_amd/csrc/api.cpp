@@ -425,7 +425,7 @@ EvolveArgs evolve_args(adscl_ctx* c, int32_t snap_every)
     a.slice = 0;
     a.order_first = 0;
     a.order_n = 0;
-    a.pad = 0;
+    a.again = 0;
     a.tail = 0;
     return a;
 }
@@ -498,13 +498,15 @@ int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const E
             e = launch_evolve_scheme(lc.cfg, c->rk, c->a_reint > 0, lc.full, n, a, s);
         } else if (n_slices > 1 && (alone(lc) || rest > 1.0)) {
             // launch k takes the instances from k * blocks on, counted round; each has
-            // n_slices turns
+            // n_slices turns, some one more, and the turns it does not need leave it where
+            // it is (segment_end)
             const int blocks = alone(lc) ? std::min(n, lc.fits) : n;
             const int launches = (int)(((int64_t)n * n_slices + blocks - 1) / blocks);
             a.slice = (int32_t)((steps + n_slices - 1) / n_slices);
             a.order_n = n;
             for (int k = 0; k < launches && e == hipSuccess; ++k) {
                 a.order_first = (int32_t)((int64_t)k * blocks % n);
+                a.again = (int64_t)k * blocks >= n;
                 e = launch_evolve(lc.cfg, lc.full, blocks, a, s);
             }
         } else {

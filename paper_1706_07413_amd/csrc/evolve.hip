@@ -52,7 +52,8 @@ struct Run {
     ADSCL_GLOBAL double* krec;  // KEEP: the current step's record
 
     // Loads instance b; false when it has already stopped (nothing to run).
-    __device__ __forceinline__ bool init(const EvolveArgs& a, int b, double* lds, int t)
+    // again: see segment_end.
+    __device__ __forceinline__ bool init(const EvolveArgs& a, int b, double* lds, int t, bool again)
     {
         st0 = a.status[b];
         if (st0.state == ST_COLLAPSED || st0.state == ST_NONFINITE) return false;
@@ -84,19 +85,8 @@ struct Run {
         stop_bits = 0;
         kp = KEEP ? gmem(a.keep[b]) : nullptr;
         krec = nullptr;
-        // Advance to the end of this segment: the call's target step, or the
-        // next snapshot step when snapshots are on.
         n = st0.steps;
-        seg_end = st0.target;
-        if (a.snap_every > 0) {
-            const int64_t nb = (n / a.snap_every + 1) * a.snap_every;
-            if (nb < seg_end) seg_end = nb;
-        }
-        if (a.slice > 0 && n + a.slice < seg_end) seg_end = n + a.slice;
-        if (a.tail > 0) {
-            const int64_t e = ic.n_final - a.tail;
-            seg_end = e < n ? n : (e < seg_end ? e : seg_end);
-        }
+        seg_end = segment_end(n, st0.target, ic.n_final, a.snap_every, a.slice, a.tail, again);
         ck_next = n;
         ck = (a.ckpt && a.ckpt_every > 0) ? gmem(a.ckpt[b]) : nullptr;
         return true;
@@ -187,10 +177,10 @@ struct Run {
 };
 
 template <int P, int W, bool FULL, bool KEEP>
-__device__ __forceinline__ void evolve_one(const EvolveArgs& a, int b, double* lds)
+__device__ __forceinline__ void evolve_one(const EvolveArgs& a, int b, double* lds, bool again)
 {
     Run<P, W, FULL, KEEP> r;
-    if (!r.init(a, b, lds, threadIdx.x)) return;
+    if (!r.init(a, b, lds, threadIdx.x, again)) return;
     r.sg.publish(r.un0, r.un1);
     while (r.n < r.seg_end) {
         r.begin_step(a);
@@ -206,12 +196,9 @@ template <int P, int W, bool FULL, bool KEEP>
 __global__ void __launch_bounds__(64 * W) evolve_kernel(EvolveArgs a)
 {
     extern __shared__ double lds[];
-    int i = blockIdx.x;
-    if (a.order_n > 0) {
-        i += a.order_first;
-        if (i >= a.order_n) i -= a.order_n;
-    }
-    evolve_one<P, W, FULL, KEEP>(a, a.order[i], lds);
+    bool again = a.again != 0;
+    const int i = launch_place((int)blockIdx.x, a.order_first, a.order_n, again);
+    evolve_one<P, W, FULL, KEEP>(a, a.order[i], lds, again);
 }
 
 // LDS doubles of one half of a pair workgroup (even, so that the second half's
@@ -236,7 +223,7 @@ __global__ void __launch_bounds__(64 * W) evolve_pair_kernel(EvolveArgs a, int n
 {
     extern __shared__ double lds[];
     if ((int)blockIdx.x < n_single) {
-        evolve_one<P, W, true, false>(a, a.order[blockIdx.x], lds);
+        evolve_one<P, W, true, false>(a, a.order[blockIdx.x], lds, false);
         return;
     }
     constexpr int WH = W / 2;
@@ -250,7 +237,7 @@ __global__ void __launch_bounds__(64 * W) evolve_pair_kernel(EvolveArgs a, int n
     // `loaded`, `run` and the exit test are uniform over each half (readfirstlane
     // makes that visible to the compiler), so the branches below are jumps of
     // whole wavefronts and no wavefront passes a barrier of the branch it skips
-    const bool loaded = __builtin_amdgcn_readfirstlane((b >= 0) && r.init(a, b, lds + half * HL, t)) != 0;
+    const bool loaded = __builtin_amdgcn_readfirstlane((b >= 0) && r.init(a, b, lds + half * HL, t, false)) != 0;
     bool run = loaded;
     // a stage of Stage::rhs passes this many barriers
     const int nbar = Stage<P, WH, true, true>::rhs_barriers(a.frozen != 0);

@@ -35,6 +35,45 @@ struct InstConst {
     double kof;       // sigma_KO/(64 h)
 };
 
+// Steps before the first of the steps that lie a multiple of K before n_final, less K:
+// segments of K steps are counted from the end of a run, and the first may be shorter.
+__host__ __device__ inline int64_t segment_phase(int64_t n_final, int64_t K) { return (K - n_final % K) % K; }
+
+// Where an instance at step n stops in one launch of the fused RK4 kernel: at its target, at
+// the next multiple of snap_every (> 0), after `slice` (> 0) steps, `tail` (> 0) steps before
+// n_final, whichever comes first.  A run to the next multiple may take several launches.
+// `again`: the instance was in an earlier one of them; it moved there unless it was at its
+// target, so a multiple it stands on now is the one it was to reach.
+__host__ __device__ inline int64_t segment_end(int64_t n, int64_t target, int64_t n_final, int32_t snap_every,
+                                               int32_t slice, int64_t tail, bool again)
+{
+    int64_t end = target;
+    if (snap_every > 0) {
+        const int64_t nb = (again && n % snap_every == 0) ? n : (n / snap_every + 1) * snap_every;
+        if (nb < end) end = nb;
+    }
+    if (slice > 0 && n + slice < end) end = n + slice;
+    if (tail > 0) {
+        const int64_t e = n_final - tail;
+        end = e < n ? n : (e < end ? e : end);
+    }
+    return end;
+}
+
+// The place in the launch order that workgroup i of a launch takes: `first` places on,
+// counted round the n there are (n = 0: i itself).  again: see segment_end.
+__host__ __device__ inline int launch_place(int i, int first, int n, bool& again)
+{
+    if (n > 0) {
+        i += first;
+        if (i >= n) {
+            i -= n;
+            again = true;
+        }
+    }
+    return i;
+}
+
 // Arguments of the fused evolution kernel (one launch per (P, W) class).
 struct EvolveArgs {
     double* Phi;            // packed state, [total]
@@ -65,15 +104,11 @@ struct EvolveArgs {
     int32_t src_every;
     int32_t a_reint;        // A evolved by Eq. (4), re-integrated every a_reint steps (0: solved)
     int32_t slice;          // fused RK4 kernel: at most this many steps (0: no limit)
-    int32_t order_first;    // fused RK4 kernel: workgroup i runs instance order[(order_first + i) mod order_n]
-    int32_t order_n;        // (order_n = 0: order[i])
-    int32_t pad;
+    int32_t order_first;    // fused RK4 kernel: workgroup i runs instance order[launch_place(i, order_first, order_n)]
+    int32_t order_n;
+    int32_t again;          // every instance of the launch was in an earlier one to the same end (segment_end)
     int64_t tail;           // fused RK4 kernel: stop this many steps before n_final (0: at the target)
 };
-
-// Steps before the first of the steps that lie a multiple of K before n_final, less K:
-// segments of K steps are counted from the end of a run, and the first may be shorter.
-__host__ __device__ inline int64_t segment_phase(int64_t n_final, int64_t K) { return (K - n_final % K) % K; }
 
 // A kernel configuration: P grid points per lane, W wavefronts per instance.
 struct ClassCfg {

@@ -1,0 +1,125 @@
+"""The host layer (csrc/api.cpp) run on the CPU, over the recorded HIP runtime of
+host_runtime.cpp: which launches a call makes, and that however a run is cut into
+launches every instance ends, and every snapshot is taken, at the step asked for."""
+import ctypes
+import math
+import os
+import random
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_1706_07413_amd import adscl
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1706_07413_amd", "csrc")
+HIP_INCLUDE = "/opt/rocm/include"
+TOTAL = 288 << 30
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(HIP_INCLUDE), reason="needs g++ and HIP's headers")
+
+_vp, _i32, _i64, _d = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_double
+
+
+@pytest.fixture(scope="module")
+def L(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("host") / "libadscl_host.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__", "-w",
+                    "-I", HIP_INCLUDE, "-o", so, os.path.join(CSRC, "api.cpp"),
+                    os.path.join(ROOT, "tests", "host_runtime.cpp")], check=True)
+    lib = ctypes.CDLL(so)
+    for name, res, args in (("adscl_create", _i32, [_vp, _vp, _vp]), ("adscl_destroy", None, [_vp]),
+                            ("adscl_init", _i32, [_vp, _vp, _vp, _i32]),
+                            ("adscl_step", _i32, [_vp, _i64, _d, _i32, _i32, _vp, _i32]),
+                            ("adscl_status", _i32, [_vp] * 6), ("adscl_last_error", ctypes.c_char_p, [_vp]),
+                            ("adscl_adjoint", _i32, [_vp, _vp, _vp, _i32, _i32, _d, _i32, _vp, _vp, _vp, _i32]),
+                            ("fake_reset", None, [_i64, _i64, _i32, _i32]), ("fake_log", ctypes.c_char_p, []),
+                            ("fake_in_use", _i64, []), ("fake_peak", _i64, []), ("fake_refused", _i64, [])):
+        getattr(lib, name).restype, getattr(lib, name).argtypes = res, args
+    lib.fake_reset(TOTAL, TOTAL, 4, 1)
+    return lib
+
+
+class Ctx:
+    """A context of the library under test on the recorded runtime."""
+
+    def __init__(self, L, Ns, cfl=0.25, n_modes=0, rk=4):
+        self.L, self.Ns = L, np.ascontiguousarray(Ns, np.int32)
+        self.cfl = cfl
+        cfg = adscl.Config(len(self.Ns), self.Ns.ctypes.data_as(ctypes.POINTER(_i32)), cfl, 0.5, 0.0, 0, n_modes, 0, rk, 0)
+        self.h = _vp()
+        assert L.adscl_create(ctypes.byref(cfg), None, ctypes.byref(self.h)) == 0, L.adscl_last_error(None)
+        self.off = np.concatenate([[0], np.cumsum(self.Ns)])
+
+    def init(self, stop=None):
+        """stop[b]: the step at which instance b collapses (0: never)."""
+        Phi = np.zeros(self.off[-1])
+        if stop is not None:
+            Phi[self.off[:-1] + 1] = stop
+        assert self.L.adscl_init(self.h, Phi.ctypes.data, np.zeros_like(Phi).ctypes.data, 0) == 0
+
+    def step(self, n, t_end=1e9, every=0, snaps=None):
+        p, k = (None, 0) if snaps is None else (snaps.ctypes.data, len(snaps))
+        rc = self.L.adscl_step(self.h, n, t_end, every, k, p, 0)
+        assert rc == 0, self.L.adscl_last_error(self.h)
+
+    def n_final(self, t):
+        return np.array([math.ceil(t / (self.cfl * (math.pi / 2) / (int(N) - 1)) - 1e-9) for N in self.Ns])
+
+    def status(self):
+        n = len(self.Ns)
+        steps, state = np.zeros(n, np.int64), np.zeros(n, np.int32)
+        assert self.L.adscl_status(self.h, None, steps.ctypes.data, state.ctypes.data, None, None) == 0
+        return steps, state
+
+    def launches(self, what="evolve "):
+        return [l for l in self.L.fake_log().decode().split("\n") if l.startswith(what)]
+
+    def close(self):
+        self.L.adscl_destroy(self.h)
+
+
+def random_batch(r):
+    """A batch past four compute units of one workgroup each, or within them."""
+    grids = r.sample([65, 129, 257, 259, 513, 1025, 1101, 2049, 4097], r.randint(1, 4))
+    Ns = [r.choice(grids) for _ in range(r.choice([3, 4, 5, 9, 14, 23]))]
+    return Ns if r.random() < 0.5 else sorted(Ns)
+
+
+@pytest.mark.parametrize("seed", range(60))
+def test_every_instance_stops_and_every_snapshot_is_taken_where_asked(L, seed):
+    """Several calls in a row, with and without snapshots, instances of which some collapse
+    on the way: the step counts and the snapshots are those of the plain rule, one launch
+    to each snapshot step."""
+    r = random.Random(seed)
+    L.fake_reset(TOTAL, TOTAL, 4, 1)
+    c = Ctx(L, random_batch(r))
+    n = len(c.Ns)
+    stop = np.array([r.choice([0, 0, 0, r.randint(1, 600)]) for _ in range(n)])
+    c.init(stop)
+    at, dead = np.zeros(n, np.int64), np.zeros(n, bool)
+    for _ in range(5):
+        k = r.choice([1, 16, 31, 32, 50, 67, 128, 200, 256, 333])
+        every = r.choice([0, 0, 1, 20, 32, 33, 48, 64, 100, 256])
+        if k / max(every, 1) > 40:
+            every = 0
+        t_end = r.choice([1e9, 1e9, 0.02, 0.05])
+        goal = np.maximum(at, np.minimum(at + k, c.n_final(t_end)))
+        slots = int(goal.max()) // every + 1 if every else 0
+        snaps = np.full((slots, 5, c.off[-1]), np.nan) if every else None
+        c.step(k, t_end, every, snaps)
+        first = at.copy()
+        hit = ~dead & (stop >= at) & (stop <= goal) & (stop > 0) & (goal > at)
+        at = np.where(dead, at, np.where(hit, stop, goal))
+        dead |= hit
+        steps, state = c.status()
+        assert np.array_equal(steps, at), (seed, k, every, t_end)
+        assert np.array_equal(state == adscl.COLLAPSED, dead)
+        for b in range(n if every else 0):
+            for s in range(slots):
+                due = first[b] <= s * every <= at[b]
+                got = snaps[s, :, c.off[b]:c.off[b + 1]]
+                assert np.all(got == s * every) if due else np.all(np.isnan(got)), (seed, b, s, k, every)
+    c.close()
