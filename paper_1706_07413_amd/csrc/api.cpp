@@ -426,6 +426,7 @@ EvolveArgs evolve_args(adscl_ctx* c, int32_t snap_every)
     a.order_first = 0;
     a.order_n = 0;
     a.again = 0;
+    a.pad = 0;
     a.tail = 0;
     return a;
 }
@@ -502,7 +503,7 @@ int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const E
             // it is (segment_end)
             const int blocks = alone(lc) ? std::min(n, lc.fits) : n;
             const int launches = (int)(((int64_t)n * n_slices + blocks - 1) / blocks);
-            a.slice = (int32_t)((steps + n_slices - 1) / n_slices);
+            a.slice = (steps + n_slices - 1) / n_slices;
             a.order_n = n;
             for (int k = 0; k < launches && e == hipSuccess; ++k) {
                 a.order_first = (int32_t)((int64_t)k * blocks % n);

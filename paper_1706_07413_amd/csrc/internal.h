@@ -45,7 +45,7 @@ __host__ __device__ inline int64_t segment_phase(int64_t n_final, int64_t K) { r
 // `again`: the instance was in an earlier one of them; it moved there unless it was at its
 // target, so a multiple it stands on now is the one it was to reach.
 __host__ __device__ inline int64_t segment_end(int64_t n, int64_t target, int64_t n_final, int32_t snap_every,
-                                               int32_t slice, int64_t tail, bool again)
+                                               int64_t slice, int64_t tail, bool again)
 {
     int64_t end = target;
     if (snap_every > 0) {
@@ -103,10 +103,11 @@ struct EvolveArgs {
     int32_t ckpt_every;
     int32_t src_every;
     int32_t a_reint;        // A evolved by Eq. (4), re-integrated every a_reint steps (0: solved)
-    int32_t slice;          // fused RK4 kernel: at most this many steps (0: no limit)
     int32_t order_first;    // fused RK4 kernel: workgroup i runs instance order[launch_place(i, order_first, order_n)]
     int32_t order_n;
     int32_t again;          // every instance of the launch was in an earlier one to the same end (segment_end)
+    int32_t pad;
+    int64_t slice;          // fused RK4 kernel: at most this many steps (0: no limit)
     int64_t tail;           // fused RK4 kernel: stop this many steps before n_final (0: at the target)
 };
 

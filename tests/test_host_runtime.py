@@ -123,3 +123,16 @@ def test_every_instance_stops_and_every_snapshot_is_taken_where_asked(L, seed):
                 got = snaps[s, :, c.off[b]:c.off[b + 1]]
                 assert np.all(got == s * every) if due else np.all(np.isnan(got)), (seed, b, s, k, every)
     c.close()
+
+
+def test_slices_past_32_bits(L):
+    """A call of 2^35 and some steps, brief by its tiny time step: the slices are not cut to
+    32 bits, and every instance ends where asked."""
+    L.fake_reset(TOTAL, TOTAL, 4, 1)
+    c = Ctx(L, [4097] * 9, cfl=1e-9)
+    c.init()
+    k = (1 << 35) + 40
+    c.step(k, 1e9)
+    steps, _ = c.status()
+    assert np.all(steps == k)
+    c.close()
