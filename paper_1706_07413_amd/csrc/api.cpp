@@ -102,6 +102,8 @@ struct adscl_ctx {
     std::map<std::string, std::pair<void*, size_t>> bufs;
     hipEvent_t fork = nullptr;  // start of a multi-class launch, recorded on `stream`
     bool paired = false;        // some class runs another's instances (pair launches)
+    // the step an instance stands on unless it has stopped; 0 while that is not known
+    std::vector<int64_t> done;
     double over = 0.0;          // one-workgroup instances, as shares of what the device holds at once
     int n_big = 0;              // classes holding one large (multi-workgroup) instance
     std::vector<BigGroup> big_groups;  // their launches
@@ -435,8 +437,10 @@ EvolveArgs evolve_args(adscl_ctx* c, int32_t snap_every)
 // its target step, or to its next multiple of snap_every when that is > 0.
 // `then`: a second launch of each class right after its first (the adjoint's forward
 // run, whose last segment is recorded; one workgroup per instance only).
+// `steps`: no one-workgroup instance takes more in this segment (0: not known), nor more
+// than `call` in all segments of the call.
 int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const EvolveArgs* then = nullptr,
-               int64_t steps = 0)
+               int64_t steps = 0, int64_t call = 0)
 {
     for (BigGroup& g : c->big_groups) {
         BigArgs x;
@@ -474,7 +478,7 @@ int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const E
     // Only where few instances stop on the way, in calls of at most a light crossing,
     // t = pi/2, of the largest grid: a launch of a whole class hands the place of an
     // instance that stops to the next at once, a slice does not.
-    const bool brief = (double)steps * c->cfl <= (double)(std::min<int64_t>(c->max_N, kMaxOneGroup) - 1);
+    const bool brief = (double)call * c->cfl <= (double)(std::min<int64_t>(c->max_N, kMaxOneGroup) - 1);
     if (steps > 0 && brief && c->over > 1.0 && pairs && !c->paired && !base.ckpt && !scheme(c))
         n_slices = (int)std::max<int64_t>(1, std::min<int64_t>(8, steps / 16));
     auto share = [](const LaunchClass& lc) { return (double)lc.inst.size() / lc.fits; };
@@ -535,13 +539,12 @@ int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const E
     return run_classes(c, launch, [&](const LaunchClass& lc) { return !alone(lc); }, follow);
 }
 
-// The same, at most `steps` steps.
-int run_evolve(adscl_ctx* c, int32_t snap_every, int64_t steps)
+// The same, one segment of a call in which no one-workgroup instance takes more than `call`
+// steps.
+int run_evolve(adscl_ctx* c, int32_t snap_every, int64_t call)
 {
-    int64_t most = 0;
-    for (const InstConst& k : c->h_ic) most = std::max(most, k.n_final);
-    if (snap_every > 0) most = std::min<int64_t>(most, snap_every);
-    return run_evolve(c, evolve_args(c, snap_every), true, nullptr, std::min(most, steps));
+    const int64_t steps = snap_every > 0 ? std::min<int64_t>(snap_every, call) : call;
+    return run_evolve(c, evolve_args(c, snap_every), true, nullptr, steps, call);
 }
 
 int run_finalize(adscl_ctx* c, bool final, int32_t snap_every, int32_t n_slots, double* snaps)
@@ -602,6 +605,14 @@ int run_call(adscl_ctx* c, int64_t max_steps, double t_end, int32_t snap_every, 
     int rc = upload_ic(c, t_end);
     if (rc) return rc;
     HIP_TRY(c, launch_set_targets(c->n_inst, c->d_ic, c->d_status, max_steps, c->stream));
+    std::vector<int64_t> goal(c->n_inst);
+    int64_t longest = 0;
+    for (int b = 0; b < c->n_inst; ++b) {
+        const int64_t left = std::max<int64_t>(0, c->h_ic[b].n_final - c->done[b]), go = std::min(left, max_steps);
+        goal[b] = c->done[b] + go;
+        if (c->N[b] <= kMaxOneGroup) longest = std::max(longest, go);
+    }
+    c->done.assign(c->n_inst, 0);
     if (snap_every > 0 && n_slots > 0) {
         if ((rc = run_finalize(c, false, snap_every, n_slots, snaps))) return rc;
         std::vector<InstStatus> st(c->n_inst);
@@ -613,13 +624,15 @@ int run_call(adscl_ctx* c, int64_t max_steps, double t_end, int32_t snap_every, 
             for (const InstStatus& s : st)
                 if ((s.state == ST_RUNNING || s.state == ST_DONE) && s.steps < s.target) more = true;
             if (!more) break;
-            if ((rc = run_evolve(c, snap_every, max_steps))) return rc;
+            if ((rc = run_evolve(c, snap_every, longest))) return rc;
             if ((rc = run_finalize(c, false, snap_every, n_slots, snaps))) return rc;
         }
     } else {
-        if ((rc = run_evolve(c, 0, max_steps))) return rc;
+        if ((rc = run_evolve(c, 0, longest))) return rc;
     }
-    return run_finalize(c, true, 0, 0, nullptr);
+    if ((rc = run_finalize(c, true, 0, 0, nullptr))) return rc;
+    c->done = std::move(goal);
+    return ADSCL_OK;
 }
 
 // A large instance whose grid synchronisation ran out of time (reported as
@@ -645,6 +658,7 @@ int after_init(adscl_ctx* c)
     double* Pi = c->state5 + c->total;
     HIP_TRY(c, launch_pins(c->n_inst, c->d_ic, Phi, Pi, c->stream));
     HIP_TRY(c, launch_reset_status(c->n_inst, c->d_status, c->stream));
+    c->done.assign(c->n_inst, 0);
     int rc = upload_ic(c, 1.0e300);
     if (rc) return rc;
     // solve the constraints at t = 0 (no step), flag collapsed / non-finite data
@@ -813,6 +827,7 @@ int adj_enqueue(adscl_ctx* c, const AdjPlan& pl, const double* d_eps, const doub
     const int J = pl.J;
     double* s5 = c->state5;
     int rc;
+    c->done.assign(n, 0);
     HIP_TRY(c, launch_init_modes(n, c->d_ic, d_eps, d_c, Jc, c->d_emode, s5, s5 + c->total, c->max_N, c->stream));
     HIP_TRY(c, launch_pins(n, c->d_ic, s5, s5 + c->total, c->stream));
     HIP_TRY(c, launch_reset_status(n, c->d_status, c->stream));
@@ -910,6 +925,12 @@ int adj_enqueue(adscl_ctx* c, const AdjPlan& pl, const double* d_eps, const doub
     HIP_TRY(c, launch_adj_finish(n, c->d_ic, c->d_status, pl.ub, c->total, c->d_emode, d_eps, Jc, pl.E0, pl.ET, J,
                                  oL, oG, oV, c->stream));
     return ADSCL_OK;
+}
+
+// After a run to the end that upload_ic was last given.
+void stands_at_end(adscl_ctx* c)
+{
+    for (int b = 0; b < c->n_inst; ++b) c->done[b] = c->h_ic[b].n_final;
 }
 
 int check_adjoint_args(adscl_ctx* c, const double* eps, const double* coef, int32_t Jc, int32_t J, double T,
@@ -1068,6 +1089,8 @@ int adscl_create(const adscl_config* cfg, void* hip_stream, adscl_ctx** out)
         TRY_C(hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking));
         c->own_stream = true;
     }
+
+    c->done.assign(c->n_inst, 0);
 
     // per-instance constants
     c->h_ic.resize(c->n_inst);
@@ -1602,6 +1625,7 @@ int adscl_adjoint(adscl_ctx* c, const double* eps, const double* coef, int32_t J
         oV = valid;
     }
     if ((rc = adj_enqueue(c, pl, d_eps, d_c, Jc, nullptr, true, oL, oG, oV))) return rc;
+    stands_at_end(c);
     c->initialized = true;
     if (mem == ADSCL_MEM_HOST) {
         HIP_TRY(c, hipMemcpyAsync(L, oL, sizeof(double) * n, hipMemcpyDeviceToHost, c->stream));
@@ -1676,6 +1700,7 @@ int adscl_descend(adscl_ctx* c, const double* eps, double* coef, int32_t Jc, int
         if (e != hipSuccess || e2 != hipSuccess)
             return fail(c, ADSCL_EHIP, std::string("graph launch: ") + hipGetErrorString(e != hipSuccess ? e : e2));
     }
+    stands_at_end(c);
     c->initialized = true;
     const hipMemcpyKind kind = mem == ADSCL_MEM_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
     HIP_TRY(c, hipMemcpyAsync(coef, d_c, sizeof(double) * (size_t)n * Jc, kind, c->stream));

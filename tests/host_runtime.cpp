@@ -147,7 +147,7 @@ hipError_t launch_evolve(ClassCfg c, bool full, int n_blocks, const EvolveArgs& 
 {
     note("evolve " + str(s) + " P" + std::to_string(c.P) + " W" + std::to_string(c.W) + " full" + std::to_string(full) +
          " blocks" + std::to_string(n_blocks) + " keep" + std::to_string(a.keep != nullptr) + " ckpt" +
-         std::to_string(a.ckpt ? a.ckpt_every : 0));
+         std::to_string(a.ckpt ? a.ckpt_every : 0) + " slice" + std::to_string(a.slice));
     for (int i = 0; i < n_blocks; ++i) {
         bool again = a.again != 0;
         const int p = launch_place(i, a.order_first, a.order_n, again);

@@ -136,3 +136,38 @@ def test_slices_past_32_bits(L):
     steps, _ = c.status()
     assert np.all(steps == k)
     c.close()
+
+
+def slices(c):
+    return [int(l.rsplit(" slice", 1)[1]) for l in c.launches()]
+
+
+def test_a_resumed_call_is_cut_by_the_steps_it_has_left(L):
+    """64 steps on from t = 1, asked for by their end time: pieces of 16, not of an eighth of
+    the whole run's."""
+    L.fake_reset(TOTAL, TOTAL, 4, 1)
+    c = Ctx(L, [4097] * 9)
+    c.init()
+    c.step(1 << 40, 1.0)
+    n = int(c.n_final(1.0)[0])
+    L.fake_reset(TOTAL, TOTAL, 4, 1)
+    c.step(1 << 40, (n + 64) * 0.25 * (math.pi / 2) / 4096)
+    assert np.all(c.status()[0] == n + 64)
+    assert set(slices(c)) == {16} and all(" blocks4 " in l for l in c.launches())
+    c.close()
+
+
+@pytest.mark.parametrize("every", [0, 64])
+def test_a_long_call_keeps_one_launch_per_class_and_interval(L, every):
+    """Past a light crossing instances stop on the way: no slices, however short the
+    snapshot intervals are."""
+    L.fake_reset(TOTAL, TOTAL, 4, 1)
+    c = Ctx(L, [257] * 9)
+    c.init()
+    n = 4 * 256 + 64 * 6  # a step is a quarter of an interval
+    snaps = np.full((n // 64 + 1, 5, c.off[-1]), np.nan) if every else None
+    c.step(n, 1e9, every, snaps)
+    assert np.all(c.status()[0] == n)
+    assert set(slices(c)) == {0} and all(" blocks9 " in l for l in c.launches())
+    assert len(c.launches()) == (n // every if every else 1)
+    c.close()
