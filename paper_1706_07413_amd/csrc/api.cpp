@@ -365,18 +365,15 @@ int buffer(adscl_ctx* c, const char* name, size_t bytes, void** out)
     return ADSCL_OK;
 }
 
-// One launch per class, the classes concurrently (on streams forked from and joined
-// back into the context stream; with `two_here` the first two one after the other on the
-// context's own).  `launch(lc, stream)` enqueues
-// the class's work.
+// One launch per selected class, the classes concurrently (one stream per class, forked
+// from and joined back into the context stream; class `here` on the context's own).
+// `launch(lc, stream)` enqueues the class's work.
 template <class F, class Sel>
-int run_classes(adscl_ctx* c, F&& launch, Sel&& selected, bool two_here = false)
+int run_classes(adscl_ctx* c, F&& launch, Sel&& selected, const LaunchClass* here = nullptr)
 {
     hipEvent_t fork = c->fork;
     if (fork) HIP_TRY(c, hipEventRecord(fork, c->stream));
-    auto stream_of = [&](const LaunchClass& lc) {
-        return lc.stream && !(two_here && &lc <= &c->classes[1]) ? lc.stream : c->stream;
-    };
+    auto stream_of = [&](const LaunchClass& lc) { return lc.stream && &lc != here ? lc.stream : c->stream; };
     for (LaunchClass& lc : c->classes) {
         if (lc.chunks > 0 || !selected(lc)) continue;
         const hipStream_t s = stream_of(lc);
@@ -384,7 +381,9 @@ int run_classes(adscl_ctx* c, F&& launch, Sel&& selected, bool two_here = false)
         HIP_TRY(c, launch(lc, s));
         if (s != c->stream) HIP_TRY(c, hipEventRecord(lc.done, s));
     }
-    // joined only now: a class on the context's stream waits for none of the others
+    // joined only now: a class whose stream shares the context's hardware queue waits for
+    // none of the others (192 ragged instances of six classes 11.7 ms, 14.6 with each joined
+    // at once)
     for (LaunchClass& lc : c->classes)
         if (lc.chunks == 0 && selected(lc) && stream_of(lc) != c->stream)
             HIP_TRY(c, hipStreamWaitEvent(c->stream, lc.done, 0));
@@ -531,12 +530,12 @@ int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const E
     };
     for (LaunchClass& lc : c->classes)
         if (alone(lc)) HIP_TRY(c, launch(lc, c->stream));
-    // Unsliced, the second class follows the first on the context's stream: beside it, its workgroups
-    // take compute units from instances of the first that have the longest way to go (the
-    // 1024-instance benchmark pass: 11.2 s against 11.5).
-    const bool follow = c->over > 1.0 && n_slices == 1 && pairs && !c->paired && !base.ckpt && !scheme(c) &&
-                        c->classes.size() - c->n_big > 2;
-    return run_classes(c, launch, [&](const LaunchClass& lc) { return !alone(lc); }, follow);
+    // Cut into slices, the largest of the others goes first, on the context's stream (1024
+    // instances of three grids, 512 steps: 20.9 ms; 22.6 where the smaller class got in first).
+    const LaunchClass* first = nullptr;
+    for (const LaunchClass& lc : c->classes)
+        if (n_slices > 1 && !first && lc.chunks == 0 && !alone(lc)) first = &lc;
+    return run_classes(c, launch, [&](const LaunchClass& lc) { return !alone(lc); }, first);
 }
 
 // The same, one segment of a call in which no one-workgroup instance takes more than `call`
@@ -1208,6 +1207,16 @@ int adscl_create(const adscl_config* cfg, void* hip_stream, adscl_ctx** out)
         std::stable_sort(lc.inst.begin(), lc.inst.end(), [&](int x, int y) { return c->N[x] > c->N[y]; });
         TRY_C(hipMalloc((void**)&lc.d_order, lc.inst.size() * sizeof(int32_t)));
         TRY_C(hipMemcpy(lc.d_order, lc.inst.data(), lc.inst.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+        // created in this order, in which the classes first appear in the batch: which of them
+        // share a hardware queue, and whose waiting workgroups a compute unit that falls free
+        // goes to, hangs on it.  Measured, one long call: 4 instances of 4097 points beside 300
+        // of 2049 and 1500 of 1025 points to t = 20 take 3.27 s, 4.6 with the largest class's
+        // stream created last; the 1024-instance benchmark pass 11.2 s, 12.6 with the largest's
+        // first.
+        if (lc.chunks == 0 && c->classes.size() > 1) {
+            TRY_C(hipStreamCreateWithFlags(&lc.stream, hipStreamNonBlocking));
+            TRY_C(hipEventCreateWithFlags(&lc.done, hipEventDisableTiming));
+        }
         if (c->flags & ADSCL_TIME_KERNELS) {
             TRY_C(hipEventCreate(&lc.t0));
             TRY_C(hipEventCreate(&lc.t1));
@@ -1224,15 +1233,6 @@ int adscl_create(const adscl_config* cfg, void* hip_stream, adscl_ctx** out)
         if ((x.chunks > 0) != (y.chunks > 0)) return y.chunks > 0;
         return 64 * x.cfg.W * x.cfg.P > 64 * y.cfg.W * y.cfg.P;
     });
-    // each class on a stream of its own, where there are several; the first class's is
-    // created last, since a process has few hardware queues and run_evolve often runs
-    // that class on the context's stream
-    for (size_t k = 1; k <= c->classes.size() && c->classes.size() > 1; ++k) {
-        LaunchClass& lc = c->classes[k % c->classes.size()];
-        if (lc.chunks > 0) continue;
-        TRY_C(hipStreamCreateWithFlags(&lc.stream, hipStreamNonBlocking));
-        TRY_C(hipEventCreateWithFlags(&lc.done, hipEventDisableTiming));
-    }
     c->n_big = 0;
     for (const LaunchClass& lc : c->classes) c->n_big += lc.chunks > 0;
     if (!scheme(c)) {

@@ -171,3 +171,25 @@ def test_a_long_call_keeps_one_launch_per_class_and_interval(L, every):
     assert set(slices(c)) == {0} and all(" blocks9 " in l for l in c.launches())
     assert len(c.launches()) == (n // every if every else 1)
     c.close()
+
+
+@pytest.mark.parametrize("Ns", [[4097] * 9 + [2049] * 9 + [1025] * 9, [4097] * 2 + [2049] * 9 + [1025] * 9,
+                                [3001, 4097, 2049, 2001, 1025, 901]])
+def test_the_classes_of_an_uncut_call_wait_for_none_of_the_others(L, Ns):
+    """Long calls and calls of a few steps: every class on a stream of its own, which waits
+    for the start of the call alone."""
+    L.fake_reset(TOTAL, TOTAL, 4, 1)
+    c = Ctx(L, Ns)
+    c.init()
+    for k in (20, 40000):
+        L.fake_reset(TOTAL, TOTAL, 4, 1)
+        c.step(k, 1e9)
+        log = L.fake_log().decode().split("\n")
+        own = [l.split()[1] for l in c.launches()]
+        n = len(set(Ns))
+        assert len(own) == n == len(set(own))
+        fork = next(l for l in log if l.startswith("record "))
+        assert fork.split()[1] not in own  # recorded on the context's stream
+        for s in own:
+            assert [l for l in log if l.startswith("wait %s " % s)] == ["wait %s %s" % (s, fork.split()[2])]
+    c.close()
