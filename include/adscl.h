@@ -195,7 +195,8 @@ int adscl_spectrum_snaps(adscl_ctx* ctx, int32_t J, int32_t n_slots, const doubl
  * the reverse sweep when those records, about 128 N_b min(ckpt_every,
  * n_final_b) bytes summed over the instances, take at most a quarter of the
  * device memory; then longer segments than ckpt_every are taken as far as their records
- * stay within a thirty-second of the device memory (and half of what is free), which
+ * stay within twice those bytes (or a 1024th of the device memory, where that is more)
+ * and within a thirty-second of the device memory, which
  * leaves less, or nothing, to recompute (unless ADSCL_ADJOINT_SEGMENTS is set to a
  * value other than 0).  Otherwise (or when the environment variable
  * ADSCL_ADJOINT_RECOMPUTE is set to a value other than 0) the recompute keeps only each

@@ -698,65 +698,27 @@ struct AdjPlan {
     AdjSeg* sgs = nullptr;
 };
 
-// Host part: step counts n_final for T, buffer sizes, per-instance pointer
-// tables, the constants upload.  Synchronises the stream.
-int adj_plan(adscl_ctx* c, double T, int64_t K, int J, AdjPlan& pl)
+// The longest segment, from `asked` steps up to `longest`, whose stage records
+// (bytes(k) of segments of k steps, not falling) stay within `room`.
+template <class Bytes>
+int64_t longer_segments(int64_t asked, int64_t longest, double room, Bytes&& bytes)
+{
+    int64_t lo = asked, hi = std::min<int64_t>(longest, INT32_MAX);
+    while (lo < hi) {
+        const int64_t mid = hi - (hi - lo) / 2;
+        if (bytes(mid) <= room) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// Buffers and per-instance pointer tables of pl for segments of K steps, nf[b] steps per
+// instance.
+int adj_buffers(adscl_ctx* c, const std::vector<int64_t>& nf, int64_t K, int J, AdjPlan& pl)
 {
     const int n = c->n_inst;
     int rc;
-    std::vector<int64_t> nf(n), ck_off(n + 1), seg_off(n + 1), stg_off(n + 1), keep_off(n + 1);
-    int64_t max_nf = 0;
-    for (int b = 0; b < n; ++b) {
-        const double r = T / c->h_ic[b].dt - 1e-9;
-        nf[b] = (r <= 0.0) ? 0 : (int64_t)std::ceil(r);
-        max_nf = std::max(max_nf, nf[b]);
-    }
-    // bytes of the stage records of segments of k steps
-    auto record_bytes = [&](int64_t k) {
-        double s = 0.0;
-        for (int b = 0; b < n; ++b)
-            s += 8.0 * (double)std::min<int64_t>(k, nf[b]) * (double)stage_record_len(c->tables[c->N[b]].cfg);
-        return s;
-    };
-    // Keep each segment's stage records from the forward run or recompute (the reverse
-    // kernel then reads the stages instead of recomputing them) when the
-    // records take at most a quarter of the device memory; ADSCL_ADJOINT_RECOMPUTE
-    // set to a value other than 0 always recomputes.
-    size_t free_b = 0, total_b = 0;
-    HIP_TRY(c, hipMemGetInfo(&free_b, &total_b));
-    auto env_set = [](const char* name) {
-        const char* v = std::getenv(name);
-        return v && v[0] && std::strcmp(v, "0") != 0;
-    };
-    const bool force = env_set("ADSCL_ADJOINT_RECOMPUTE");
-    pl.stored = !force && record_bytes(K) <= (double)(total_b / 4);
-    // Segments longer than asked for where their records are small: the forward run
-    // records its last segment itself, so what fits in one is computed once instead of
-    // twice (N = 4097, 1043 steps in segments of 512: 50 ms a gradient with the last
-    // segment recorded, 43 with all of them).  Within a thirty-second of the device
-    // memory, and within half of what is free beside the records held already.
-    // ADSCL_ADJOINT_SEGMENTS set to a value other than 0 takes them as asked for.
-    const int64_t asked = K;
-    if (pl.stored && !env_set("ADSCL_ADJOINT_SEGMENTS")) {
-        const double room = std::min((double)(total_b / 32), 0.5 * (double)free_b + (double)c->bufs["keep"].second);
-        int64_t lo = K, hi = max_nf;  // record_bytes does not fall
-        while (lo < hi) {
-            const int64_t mid = hi - (hi - lo) / 2;
-            if (record_bytes(mid) <= room) lo = mid;
-            else hi = mid - 1;
-        }
-        K = std::min<int64_t>(lo, INT32_MAX);
-    }
-    void* keep = nullptr;
-    if (pl.stored) {
-        rc = buffer(c, "keep", (size_t)record_bytes(K), &keep);
-        if (rc == ADSCL_ENOMEM && K > asked) {
-            (void)hipGetLastError();
-            K = asked;
-            rc = buffer(c, "keep", (size_t)record_bytes(K), &keep);
-        }
-        if (rc) return rc;
-    }
+    std::vector<int64_t> ck_off(n + 1), seg_off(n + 1), stg_off(n + 1), keep_off(n + 1);
     pl.J = J;
     pl.K = K;
     pl.max_seg = 0;
@@ -768,13 +730,14 @@ int adj_plan(adscl_ctx* c, double T, int64_t K, int J, AdjPlan& pl)
         keep_off[b + 1] = keep_off[b] + std::min<int64_t>(K, nf[b]) * (int64_t)stage_record_len(t.cfg);
         pl.max_seg = std::max<int64_t>(pl.max_seg, (nf[b] + K - 1) / K);
     }
-    void *ck, *seg, *stg, *ub, *u0, *dummy, *spec, *ptrs, *rst, *sgs;
+    void *ck, *seg, *stg, *keep = nullptr, *ub, *u0, *dummy, *spec, *ptrs, *rst, *sgs;
     const size_t nJ = (size_t)n * J;
-    if ((rc = buffer(c, "ckpt", sizeof(double) * ck_off[n], &ck))) return rc;
     if (pl.stored) {
+        if ((rc = buffer(c, "keep", sizeof(double) * keep_off[n], &keep))) return rc;
         seg_off.assign(n + 1, 0);  // no per-step states needed, nor scratch to recompute stages in
         stg_off.assign(n + 1, 0);
     }
+    if ((rc = buffer(c, "ckpt", sizeof(double) * ck_off[n], &ck))) return rc;
     if ((rc = buffer(c, "seg", sizeof(double) * seg_off[n], &seg))) return rc;
     if ((rc = buffer(c, "stage", sizeof(double) * stg_off[n], &stg))) return rc;
     if ((rc = buffer(c, "ubar", sizeof(double) * 2 * c->total, &ub))) return rc;
@@ -808,7 +771,65 @@ int adj_plan(adscl_ctx* c, double T, int64_t K, int J, AdjPlan& pl)
     }
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     HIP_TRY(c, hipMemcpy(ptrs, hp.data(), sizeof(double*) * 4 * n, hipMemcpyHostToDevice));
+    return ADSCL_OK;
+}
+
+// Host part: step counts n_final for T, the length of the segments, buffers and the
+// constants upload.  Synchronises the stream.  The last of a call's allocations.
+int adj_plan(adscl_ctx* c, double T, int64_t K, int J, AdjPlan& pl)
+{
+    const int n = c->n_inst;
+    int rc;
+    std::vector<int64_t> nf(n);
+    int64_t max_nf = 0;
+    for (int b = 0; b < n; ++b) {
+        const double r = T / c->h_ic[b].dt - 1e-9;
+        nf[b] = (r <= 0.0) ? 0 : (int64_t)std::ceil(r);
+        max_nf = std::max(max_nf, nf[b]);
+    }
+    // bytes of the stage records of segments of k steps
+    auto record_bytes = [&](int64_t k) {
+        double s = 0.0;
+        for (int b = 0; b < n; ++b)
+            s += 8.0 * (double)std::min<int64_t>(k, nf[b]) * (double)stage_record_len(c->tables[c->N[b]].cfg);
+        return s;
+    };
+    // Keep each segment's stage records from the forward run or recompute (the reverse
+    // kernel then reads the stages instead of recomputing them) when the
+    // records take at most a quarter of the device memory; ADSCL_ADJOINT_RECOMPUTE
+    // set to a value other than 0 always recomputes.
+    size_t free_b = 0, total_b = 0;
+    HIP_TRY(c, hipMemGetInfo(&free_b, &total_b));
+    auto env_set = [](const char* name) {
+        const char* v = std::getenv(name);
+        return v && v[0] && std::strcmp(v, "0") != 0;
+    };
+    const bool force = env_set("ADSCL_ADJOINT_RECOMPUTE");
+    pl.stored = !force && record_bytes(K) <= (double)(total_b / 4);
+    // Segments longer than asked for where their records are small: the forward run
+    // records its last segment itself, so what fits in one is computed once instead of
+    // twice (N = 4097, 1043 steps in segments of 512: 50 ms a gradient with the last
+    // segment recorded, 43 with twice that or all of them).  The records stay within twice
+    // what the caller's interval takes (or a 1024th of the device memory, where that is
+    // more) and within a thirty-second of the device memory, whatever is free at the
+    // moment, so that a call takes the same course each time.
+    // ADSCL_ADJOINT_SEGMENTS set to a value other than 0 takes them as asked for.
+    int64_t longer = K;
+    if (pl.stored && !env_set("ADSCL_ADJOINT_SEGMENTS")) {
+        const double room = std::min(std::max(2.0 * record_bytes(K), (double)(total_b / 1024)), (double)(total_b / 32));
+        longer = longer_segments(K, max_nf, room, record_bytes);
+    }
     if ((rc = spec_rows(c, 1))) return rc;
+    rc = adj_buffers(c, nf, longer, J, pl);
+    if (rc == ADSCL_ENOMEM && longer > K) {  // as asked for, then
+        (void)hipGetLastError();
+        auto& keep = c->bufs["keep"];
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        if (keep.first) HIP_TRY(c, hipFree(keep.first));
+        keep = {nullptr, 0};
+        rc = adj_buffers(c, nf, K, J, pl);
+    }
+    if (rc) return rc;
     return upload_ic(c, T);
 }
 
@@ -1612,10 +1633,10 @@ int adscl_adjoint(adscl_ctx* c, const double* eps, const double* coef, int32_t J
     const int n = c->n_inst;
     double *d_eps, *d_c;
     if ((rc = stage_inputs(c, eps, coef, Jc, mem, &d_eps, &d_c))) return rc;
-    AdjPlan pl;
-    if ((rc = adj_plan(c, T, ckpt_every, J, pl))) return rc;
     void* outs;
     if ((rc = buffer(c, "outs", sizeof(double) * ((size_t)n * Jc + 2 * n), &outs))) return rc;
+    AdjPlan pl;
+    if ((rc = adj_plan(c, T, ckpt_every, J, pl))) return rc;
     double* oL = (double*)outs;
     double* oG = oL + n;
     int32_t* oV = (int32_t*)(oG + (size_t)n * Jc);
@@ -1650,8 +1671,6 @@ int adscl_descend(adscl_ctx* c, const double* eps, double* coef, int32_t Jc, int
     const int n = c->n_inst;
     double *d_eps, *d_c;
     if ((rc = stage_inputs(c, eps, coef, Jc, mem, &d_eps, &d_c))) return rc;
-    AdjPlan pl;
-    if ((rc = adj_plan(c, T, ckpt_every, J, pl))) return rc;
     void *g, *lv, *vv, *st, *act, *it, *hist;
     if ((rc = buffer(c, "gd_grad", sizeof(double) * (size_t)n * Jc, &g))) return rc;
     if ((rc = buffer(c, "gd_L", sizeof(double) * n, &lv))) return rc;
@@ -1660,6 +1679,8 @@ int adscl_descend(adscl_ctx* c, const double* eps, double* coef, int32_t Jc, int
     if ((rc = buffer(c, "gd_active", sizeof(int32_t) * n, &act))) return rc;
     if ((rc = buffer(c, "gd_iter", sizeof(int32_t), &it))) return rc;
     if ((rc = buffer(c, "gd_hist", sizeof(double) * (size_t)iters * n, &hist))) return rc;
+    AdjPlan pl;
+    if ((rc = adj_plan(c, T, ckpt_every, J, pl))) return rc;
     GdState gs;
     gs.s = (double*)st;
     gs.Lprev = (double*)st + n;

@@ -193,3 +193,76 @@ def test_the_classes_of_an_uncut_call_wait_for_none_of_the_others(L, Ns):
         for s in own:
             assert [l for l in log if l.startswith("wait %s " % s)] == ["wait %s %s" % (s, fork.split()[2])]
     c.close()
+
+
+def adjoint(c, K, T):
+    """One gradient; (return code, steps of a segment, segments)."""
+    n = len(c.Ns)
+    c.L.fake_reset(TOTAL, c.limit, 4, 1)
+    eps, coef, out, valid = np.ones(n), np.ones((n, 1)), np.zeros((2, n)), np.zeros(n, np.int32)
+    rc = c.L.adscl_adjoint(c.h, eps.ctypes.data, coef.ctypes.data, 1, 1, T, K, out[0].ctypes.data, out[1].ctypes.data,
+                           valid.ctypes.data, 0)
+    seg = c.launches("segment ")
+    assert rc or np.all(valid == 1) and np.all(c.status()[0] == c.n_final(T))
+    return rc, int(seg[0].split()[3]) if seg else 0, len(seg)
+
+
+RECORD = 128 * 4096  # bytes of a step's stage record at N = 4097
+
+
+@pytest.mark.parametrize("Ns,K,T,want", [
+    ([4097], 512, 0.1, 1024),           # 1043 steps: twice the interval
+    ([4097], 512, 0.05, 522),           # 522 steps: all of them
+    ([4097] * 6, 256, 0.1, 512),
+    ([4097] * 3, 1, 0.1, 192),          # a 1024th of the device memory
+    ([4097, 1025], 4096, 0.1, 4096),    # as asked: longer than the run
+])
+def test_the_adjoint_holds_what_its_interval_asks_for_or_twice_that(L, Ns, K, T, want):
+    """The records follow ckpt_every, whatever is free at the moment of the call."""
+    for limit in (TOTAL, L.fake_in_use() + (5 << 30)):
+        L.fake_reset(TOTAL, TOTAL, 4, 1)
+        c = Ctx(L, Ns, n_modes=1)
+        c.limit = limit
+        held = L.fake_in_use()
+        rc, k, _ = adjoint(c, K, T)
+        assert (rc, k) == (0, want)
+        nf = c.n_final(T)
+        asked = RECORD * np.minimum(K, nf)[np.array(Ns) == 4097].sum()
+        rest = sum(8 * N * (2 * (int(n) // k + 3) + 8) for N, n in zip(Ns, nf)) + (1 << 20)
+        assert L.fake_in_use() - held <= max(2 * asked, TOTAL // 1024) + rest
+        c.close()
+
+
+def test_the_adjoint_takes_its_interval_as_asked_where_more_does_not_fit(L, monkeypatch):
+    """Every amount of memory between what the interval as asked needs and what longer
+    segments need: the call succeeds, and an allocation that failed leaves nothing behind."""
+    sizes = {}
+    for env in ("", "1"):
+        monkeypatch.setenv("ADSCL_ADJOINT_SEGMENTS", env)
+        L.fake_reset(TOTAL, TOTAL, 4, 1)
+        c = Ctx(L, [4097] * 2, n_modes=1)
+        c.limit = TOTAL
+        base = L.fake_in_use()
+        _, k, _ = adjoint(c, 400, 0.1)
+        sizes[env] = (k, L.fake_in_use() - base)
+        c.close()
+    monkeypatch.setenv("ADSCL_ADJOINT_SEGMENTS", "")
+    assert sizes["1"][0] == 400 and sizes[""][0] == 800 and sizes[""][1] > sizes["1"][1]
+    lo, hi = sizes["1"][1], sizes[""][1]
+    for limit in [lo, lo + 1, (lo + hi) // 2, hi - 65 * 4096 * 10, hi - 65536, hi - 1, hi, hi + 1]:
+        L.fake_reset(TOTAL, TOTAL, 4, 1)
+        c = Ctx(L, [4097] * 2, n_modes=1)
+        c.limit = base + limit
+        rc, k, n = adjoint(c, 400, 0.1)
+        assert rc == 0 and k == (800 if limit >= hi else 400) and n == -(-1043 // k), (limit - lo, hi - limit, rc, k)
+        assert L.fake_in_use() <= c.limit and (L.fake_refused() > 0) == (limit < hi)
+        rc, k2, _ = adjoint(c, 400, 0.1)  # and again, with what it now holds
+        assert rc == 0 and k2 == k
+        c.close()
+    L.fake_reset(TOTAL, TOTAL, 4, 1)
+    c = Ctx(L, [4097] * 2, n_modes=1)
+    c.limit = base + lo - 4096
+    assert adjoint(c, 400, 0.1)[0] == adscl.ENOMEM
+    c.limit = TOTAL
+    assert adjoint(c, 400, 0.1)[:2] == (0, 800)
+    c.close()
