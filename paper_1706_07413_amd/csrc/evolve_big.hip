@@ -84,7 +84,21 @@ constexpr int XW_BITS = kSlots * XW_N;  // then, slot by step, the chunk's colla
 static_assert(kBigRecWords == XW_BITS + 16, "record size");
 
 constexpr u64 kEmpty = 0x7ff4c0de5eedface;
-constexpr unsigned kSpinLimit = 1u << 22;  // about seconds: legitimate waits are microseconds
+
+// How long a wait has gone on: it gives up after 2^31 ticks of the 100 MHz wall clock
+// (21 s), looked at every 256th poll, whatever a poll takes.  Legitimate waits are
+// microseconds, save for workgroups of the launch that have yet to start, since another
+// stream's kernel may hold their compute units for seconds.
+struct Wait {
+    unsigned polls = 0;
+    u64 since = 0;
+    __device__ __forceinline__ bool look() { return (++polls & 255) == 0; }
+    __device__ __forceinline__ bool over(u64 now)
+    {
+        if (polls == 256) since = now;
+        return now - since > 1ull << 31;
+    }
+};
 
 __device__ __forceinline__ void put(ADSCL_GLOBAL u64* w, double v)
 {
@@ -205,7 +219,7 @@ struct Helper {
 #pragma unroll
         for (int k = 0; k < NW; ++k) w[k] = 0;
         bool ok = true;
-        for (unsigned n = 1;; ++n) {
+        for (Wait wait;;) {
             bool miss = false;
             if (act) {
 #pragma unroll
@@ -214,8 +228,8 @@ struct Helper {
                 for (int k = 0; k < NW; ++k) miss |= w[k] == kEmpty;
             }
             if (!__any(miss)) break;
-            if ((n & 255) == 0 &&
-                (n > kSpinLimit || __hip_atomic_load(c.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+            if (wait.look() &&
+                (wait.over(wall_clock64()) || __hip_atomic_load(c.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
                 __hip_atomic_store(c.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 ok = false;
                 break;
