@@ -100,10 +100,13 @@ struct Wait {
     }
 };
 
+// The word that carries v, never kEmpty: a signalling NaN (data could hold that pattern)
+// becomes a quiet one.
+__device__ __forceinline__ u64 word_of(double v) { return (u64)__double_as_longlong(__builtin_canonicalize(v)); }
+
 __device__ __forceinline__ void put(ADSCL_GLOBAL u64* w, double v)
 {
-    // a signalling NaN (data could hold kEmpty) becomes a quiet one
-    __hip_atomic_store(w, (u64)__double_as_longlong(__builtin_canonicalize(v)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(w, word_of(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ void clear(ADSCL_GLOBAL u64* w)

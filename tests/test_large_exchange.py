@@ -48,3 +48,38 @@ int main()
 """
     for t in run(tmp_path, "g++", code):
         assert 10e8 < int(t) < 30e8, t
+
+
+@pytest.mark.skipif(not os.path.exists(CLANG), reason="needs ROCm's clang++")
+def test_no_value_is_sent_as_the_empty_word(tmp_path):
+    """The pattern of an empty word, as data, goes out as a quiet NaN; every other value as
+    it is.  (Through the library such data never reach the exchange: the constraint solve
+    after adscl_init marks the instance non-finite, and the kernel skips it.)"""
+    code = source(r"constexpr u64 kEmpty = [^\n]*\n") + r"""
+static long long __double_as_longlong(double v)
+{
+    long long b;
+    std::memcpy(&b, &v, 8);
+    return b;
+}
+""" + source(r"__device__ __forceinline__ u64 word_of\(double v\) \{[^\n]*\n") + r"""
+static double value(u64 b)
+{
+    double v;
+    std::memcpy(&v, &b, 8);
+    return v;
+}
+int main()
+{
+    std::printf("%llx\n", (u64)(kEmpty ^ word_of(value(kEmpty))));
+    // zeros, the smallest and largest numbers, infinities, quiet NaNs
+    for (u64 b : {0ull, 1ull << 63, 1ull, (1ull << 63) | 1, 0x000fffffffffffffull, 0x7fefffffffffffffull,
+                  0x3ff0000000000001ull, 0x7ff0000000000000ull, 0xfff0000000000000ull, 0x7ff8000000000000ull,
+                  0xfff8000000000123ull})
+        std::printf("%llx\n", (u64)(b ^ word_of(value(b))));
+    return 0;
+}
+"""
+    out = run(tmp_path, CLANG, code)
+    assert int(out[0], 16) == 1 << 51  # the quiet bit
+    assert set(out[1:]) == {"0"}
