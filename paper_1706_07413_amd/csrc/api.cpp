@@ -470,9 +470,9 @@ int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const E
     // workgroups of several classes holds fewer wavefronts); the others then run side
     // by side.
     // Measured, ms, against every class in one launch on a stream of its own: 1024
-    // instances of 1025, 2049 and 4097 points, 512 steps, 26.4 -> 21.1; 250 + 324 + 349 of
-    // 4097, 2049 and 1025, 256 steps, 11.3 -> 8.9; 300 of 4097, 8.5 -> 5.3; 600 of 2049,
-    // 6.5 -> 4.9 (4 to 32 slices are alike).
+    // instances of 1025, 2049 and 4097 points, 512 steps, 26.7 -> 20.8; 250 + 324 + 349 of
+    // 4097, 2049 and 1025, 256 steps, 10.5 -> 8.8 (11.1 where the runtime gives the last two
+    // one hardware queue); 300 of 4097, 8.5 -> 5.3; 600 of 2049, 6.5 -> 5.0.
     int n_slices = 1;
     // Only where few instances stop on the way, in calls of at most a light crossing,
     // t = pi/2, of the largest grid: a launch of a whole class hands the place of an
@@ -480,6 +480,13 @@ int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const E
     const bool brief = (double)call * c->cfl <= (double)(std::min<int64_t>(c->max_N, kMaxOneGroup) - 1);
     if (steps > 0 && brief && c->over > 1.0 && pairs && !c->paired && !base.ckpt && !scheme(c))
         n_slices = (int)std::max<int64_t>(1, std::min<int64_t>(8, steps / 16));
+    // And only where they save a tenth: in rounds of the device, `over` rounded up to a
+    // slice instead of to a whole round, with a step's time for each slice's start
+    // (against one launch per class: 12000 instances of 65 points, 64 steps, 4.3 ms in
+    // slices, 4.0 without; 5000 of 1025 6.2 and 5.4; 2000 of 4097, 48 steps, 6.7 and 6.4).
+    if (std::ceil(c->over * n_slices) / n_slices * (1.0 + n_slices / (double)std::max<int64_t>(1, steps)) >
+        0.9 * std::ceil(c->over))
+        n_slices = 1;
     auto share = [](const LaunchClass& lc) { return (double)lc.inst.size() / lc.fits; };
     auto alone = [&](const LaunchClass& lc) { return n_slices > 1 && lc.chunks == 0 && share(lc) >= 0.8; };
     double rest = c->over;

@@ -266,3 +266,16 @@ def test_the_adjoint_takes_its_interval_as_asked_where_more_does_not_fit(L, monk
     c.limit = TOTAL
     assert adjoint(c, 400, 0.1)[:2] == (0, 800)
     c.close()
+
+
+@pytest.mark.parametrize("n,steps,cut", [(5, 512, True), (9, 64, True), (9, 31, False), (7, 64, False), (7, 512, True), (8, 512, False),
+                                         (40, 64, False), (41, 4096, False)])
+def test_slices_only_where_the_last_round_is_nearly_empty(L, n, steps, cut):
+    """n instances on four compute units: cut where a tenth of the rounds is saved."""
+    L.fake_reset(TOTAL, TOTAL, 4, 1)
+    c = Ctx(L, [4097] * n)
+    c.init()
+    c.step(steps, 1e9)
+    assert (len(c.launches()) > 1) == cut
+    assert np.all(c.status()[0] == steps)
+    c.close()
