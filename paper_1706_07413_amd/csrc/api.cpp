@@ -63,7 +63,7 @@ struct BigGroup {
 struct NTables {
     ClassCfg cfg;
     double* d_tab = nullptr;     // lane-interleaved sc, t2, ct2 for cfg
-    double* d_nat = nullptr;     // tables in grid order (kNat*)
+    double* d_nat = nullptr;     // tables in grid order (kNat*), in d_tab's allocation
     double* d_emode = nullptr;   // e_j(x_i), [J][N]
     double* d_wPi = nullptr;     // h tan^2 x e_j, [J][N]
     double* d_wPhi = nullptr;    // h tan^2 x e_j'/omega_j, [J][N]
@@ -89,7 +89,7 @@ struct adscl_ctx {
     InstStatus* d_status = nullptr;
     InstConst* d_ic = nullptr;
     std::vector<InstConst> h_ic;
-    const double** d_tab = nullptr;
+    const double** d_tab = nullptr;  // per instance, as the four below, in its allocation
     const double** d_nat = nullptr;
     const double** d_emode = nullptr;
     const double** d_wPi = nullptr;
@@ -250,6 +250,18 @@ void host_tables(int N, ClassCfg cfg, std::vector<double>& tab, std::vector<doub
         nat[(size_t)kNatCT2 * N + i] = v[2];
         nat[(size_t)kNatRA * N + i] = (double)((1.0L + 2.0L * s * s) / (s * c));
     }
+}
+
+// Both of those on the device, one after the other in one allocation.
+hipError_t upload_tables(NTables& t, std::vector<double>& tab, const std::vector<double>& nat)
+{
+    const size_t first = tab.size();
+    tab.insert(tab.end(), nat.begin(), nat.end());
+    const size_t bytes = tab.size() * sizeof(double);
+    hipError_t e = hipMalloc((void**)&t.d_tab, bytes);
+    if (e != hipSuccess) return e;
+    t.d_nat = t.d_tab + first;
+    return hipMemcpy(t.d_tab, tab.data(), bytes, hipMemcpyHostToDevice);
 }
 
 // Linear AdS4 eigenmodes e_j(x) = d_j cos^3 x P_j^(1/2,3/2)(cos 2x), unit norm in
@@ -1161,10 +1173,7 @@ int adscl_create(const adscl_config* cfg, void* hip_stream, adscl_ctx** out)
                 TRY_C(prepare_evolve_big(cfg, c->rk, c->a_reint > 0, c->max_lds));
                 std::vector<double> tab, nat, e, wpi, wphi;
                 host_tables(N, cfg, tab, nat, G);
-                TRY_C(hipMalloc((void**)&t.d_tab, tab.size() * sizeof(double)));
-                TRY_C(hipMemcpy(t.d_tab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice));
-                TRY_C(hipMalloc((void**)&t.d_nat, nat.size() * sizeof(double)));
-                TRY_C(hipMemcpy(t.d_nat, nat.data(), nat.size() * sizeof(double), hipMemcpyHostToDevice));
+                TRY_C(upload_tables(t, tab, nat));
                 if (c->n_modes > 0) {
                     host_modes(N, c->n_modes, e, wpi, wphi);
                     const size_t bytes = e.size() * sizeof(double);
@@ -1202,10 +1211,7 @@ int adscl_create(const adscl_config* cfg, void* hip_stream, adscl_ctx** out)
             TRY_C(prepare_adjoint(t.cfg, c->max_lds));
             std::vector<double> tab, nat, e, wpi, wphi;
             host_tables(N, t.cfg, tab, nat);
-            TRY_C(hipMalloc((void**)&t.d_tab, tab.size() * sizeof(double)));
-            TRY_C(hipMemcpy(t.d_tab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice));
-            TRY_C(hipMalloc((void**)&t.d_nat, nat.size() * sizeof(double)));
-            TRY_C(hipMemcpy(t.d_nat, nat.data(), nat.size() * sizeof(double), hipMemcpyHostToDevice));
+            TRY_C(upload_tables(t, tab, nat));
             if (c->n_modes > 0) {
                 host_modes(N, c->n_modes, e, wpi, wphi);
                 const size_t bytes = e.size() * sizeof(double);
@@ -1351,26 +1357,19 @@ int adscl_create(const adscl_config* cfg, void* hip_stream, adscl_ctx** out)
         TRY_C(hipMemset(g.err, 0, sizeof(int32_t) * desc.size()));
     }
 
-    std::vector<const double*> tabp(c->n_inst), natp(c->n_inst), ep(c->n_inst), wpp(c->n_inst), wfp(c->n_inst);
-    for (int b = 0; b < c->n_inst; ++b) {
+    const size_t n = c->n_inst;
+    std::vector<const double*> ptrs(5 * n);
+    for (size_t b = 0; b < n; ++b) {
         const NTables& t = c->tables[c->N[b]];
-        tabp[b] = t.d_tab;
-        natp[b] = t.d_nat;
-        ep[b] = t.d_emode;
-        wpp[b] = t.d_wPi;
-        wfp[b] = t.d_wPhi;
+        const double* const of[5] = {t.d_tab, t.d_nat, t.d_emode, t.d_wPi, t.d_wPhi};
+        for (int k = 0; k < 5; ++k) ptrs[k * n + b] = of[k];
     }
-    const size_t pb = sizeof(double*) * c->n_inst;
-    TRY_C(hipMalloc((void**)&c->d_tab, pb));
-    TRY_C(hipMalloc((void**)&c->d_nat, pb));
-    TRY_C(hipMemcpy(c->d_nat, natp.data(), pb, hipMemcpyHostToDevice));
-    TRY_C(hipMalloc((void**)&c->d_emode, pb));
-    TRY_C(hipMalloc((void**)&c->d_wPi, pb));
-    TRY_C(hipMalloc((void**)&c->d_wPhi, pb));
-    TRY_C(hipMemcpy(c->d_tab, tabp.data(), pb, hipMemcpyHostToDevice));
-    TRY_C(hipMemcpy(c->d_emode, ep.data(), pb, hipMemcpyHostToDevice));
-    TRY_C(hipMemcpy(c->d_wPi, wpp.data(), pb, hipMemcpyHostToDevice));
-    TRY_C(hipMemcpy(c->d_wPhi, wfp.data(), pb, hipMemcpyHostToDevice));
+    TRY_C(hipMalloc((void**)&c->d_tab, sizeof(double*) * ptrs.size()));
+    TRY_C(hipMemcpy(c->d_tab, ptrs.data(), sizeof(double*) * ptrs.size(), hipMemcpyHostToDevice));
+    c->d_nat = c->d_tab + n;
+    c->d_emode = c->d_tab + 2 * n;
+    c->d_wPi = c->d_tab + 3 * n;
+    c->d_wPhi = c->d_tab + 4 * n;
 
     TRY_C(hipMalloc((void**)&c->state5, sizeof(double) * 5 * (size_t)c->total));
     TRY_C(hipMemset(c->state5, 0, sizeof(double) * 5 * (size_t)c->total));
@@ -1405,16 +1404,11 @@ void adscl_destroy(adscl_ctx* c)
     }
     for (auto& kv : c->tables) {
         if (kv.second.d_tab) (void)hipFree(kv.second.d_tab);
-        if (kv.second.d_nat) (void)hipFree(kv.second.d_nat);
         if (kv.second.d_emode) (void)hipFree(kv.second.d_emode);
         if (kv.second.d_wPi) (void)hipFree(kv.second.d_wPi);
         if (kv.second.d_wPhi) (void)hipFree(kv.second.d_wPhi);
     }
     if (c->d_tab) (void)hipFree((void*)c->d_tab);
-    if (c->d_nat) (void)hipFree((void*)c->d_nat);
-    if (c->d_emode) (void)hipFree((void*)c->d_emode);
-    if (c->d_wPi) (void)hipFree((void*)c->d_wPi);
-    if (c->d_wPhi) (void)hipFree((void*)c->d_wPhi);
     if (c->state5) (void)hipFree(c->state5);
     if (c->d_status) (void)hipFree(c->d_status);
     if (c->d_ic) (void)hipFree(c->d_ic);

@@ -18,6 +18,7 @@ std::string g_log;                  // one line per recorded call
 std::map<void*, size_t> g_held;     // device allocations
 size_t g_total = (size_t)288 << 30, g_limit = ~(size_t)0, g_in_use = 0, g_peak = 0;
 size_t g_refused = 0;               // allocations past the limit
+long long g_setup = 0;              // allocations and copies
 hipError_t g_last = hipSuccess;
 int g_cus = 4, g_per_cu = 1;
 intptr_t g_streams = 0;
@@ -38,16 +39,19 @@ void fake_reset(long long total, long long limit, int cus, int per_cu)
     g_per_cu = per_cu;
     g_peak = g_in_use;
     g_refused = 0;
+    g_setup = 0;
     g_last = hipSuccess;
 }
 const char* fake_log() { return g_log.c_str(); }
 long long fake_in_use() { return (long long)g_in_use; }
 long long fake_peak() { return (long long)g_peak; }
+long long fake_setup() { return g_setup; }
 long long fake_refused() { return (long long)g_refused; }
 
 // ---- the runtime ----
 hipError_t hipMalloc(void** p, size_t n)
 {
+    ++g_setup;
     if (n > g_limit - g_in_use) {
         ++g_refused;
         return g_last = hipErrorOutOfMemory;
@@ -75,7 +79,7 @@ hipError_t hipMemGetInfo(size_t* free_b, size_t* total)
     *free_b = (g_limit < g_total ? g_limit : g_total) - g_in_use;
     return hipSuccess;
 }
-hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { ++g_setup; std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t) { return hipMemcpy(d, s, n, k); }
 hipError_t hipMemset(void* d, int v, size_t n) { std::memset(d, v, n); return hipSuccess; }
 hipError_t hipGetLastError() { const hipError_t e = g_last; g_last = hipSuccess; return e; }

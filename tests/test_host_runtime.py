@@ -36,7 +36,7 @@ def L(tmp_path_factory):
                             ("adscl_status", _i32, [_vp] * 6), ("adscl_last_error", ctypes.c_char_p, [_vp]),
                             ("adscl_adjoint", _i32, [_vp, _vp, _vp, _i32, _i32, _d, _i32, _vp, _vp, _vp, _i32]),
                             ("fake_reset", None, [_i64, _i64, _i32, _i32]), ("fake_log", ctypes.c_char_p, []),
-                            ("fake_in_use", _i64, []), ("fake_peak", _i64, []), ("fake_refused", _i64, [])):
+                            ("fake_in_use", _i64, []), ("fake_setup", _i64, []), ("fake_peak", _i64, []), ("fake_refused", _i64, [])):
         getattr(lib, name).restype, getattr(lib, name).argtypes = res, args
     lib.fake_reset(TOTAL, TOTAL, 4, 1)
     return lib
@@ -279,3 +279,19 @@ def test_slices_only_where_the_last_round_is_nearly_empty(L, n, steps, cut):
     assert (len(c.launches()) > 1) == cut
     assert np.all(c.status()[0] == steps)
     c.close()
+
+
+def test_creating_a_context_takes_few_allocations_and_copies(L):
+    """One of each for a grid size's coefficient tables, its launch order, the pointer tables
+    and the instances' constants; and the state, the status and the staging buffer.  Nothing
+    is left when it goes."""
+    held = L.fake_in_use()
+    L.fake_reset(TOTAL, TOTAL, 4, 1)
+    c = Ctx(L, [17] * 10)
+    assert L.fake_setup() <= 2 * 4 + 3
+    c.close()
+    c = Ctx(L, [17, 65, 4097, 1101], n_modes=2)
+    c.init()
+    c.step(10)
+    c.close()
+    assert L.fake_in_use() == held
