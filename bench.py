@@ -215,7 +215,7 @@ def single_instance_rates(adscl, steps):
 
 def large_instance_rate(adscl, steps=4096):
     """The 16385-point two-mode instance (0.05 (e_0 + 0.6 e_1), boundary time)
-    alone on the GPU: 8 cooperating workgroups of 2048 points each."""
+    alone on the GPU: 22 cooperating workgroups of 768 points each."""
     from paper_1706_07413_amd import inputs as I
     cfg = I.config1()
     b = adscl.Batch(cfg["N"], gauge=cfg["gauge"], a_collapse=cfg["a_collapse"], n_modes=2)

@@ -12,8 +12,9 @@
  *
  * Layout: instance b has an odd grid size N_b (17 <= N_b <= 65537), h_b =
  * (pi/2)/(N_b-1), x_i = i h_b.  An instance with N_b <= 4097 is evolved by one
- * workgroup; a larger one by several cooperating workgroups (chunks of 2048
- * points, launched before the others in each call).  Every per-point array is packed: instance b
+ * workgroup; a larger one by several cooperating workgroups (chunks of 768
+ * points, 1024 or 2048 where the grid needs them, launched before the others in each
+ * call).  Every per-point array is packed: instance b
  * occupies [off_b, off_b + N_b) with off_b the exclusive prefix sum of N_b, in
  * the order the instances were given to adscl_create.
  *
@@ -124,7 +125,7 @@ int adscl_init_modes(adscl_ctx* ctx, const double* eps, const double* c, int32_t
  * to snaps[slot][field][sum N_b] (5 fields, m the mass function
  * (1-A) sin x / cos^3 x).  snaps may be NULL when snap_every == 0.
  * ADSCL_EHIP also when the workgroups of a large instance (N_b > 4097) stopped
- * waiting for each other (a bounded wait of seconds; the instance is then left
+ * waiting for each other (a wait is given up after 21 seconds; the instance is then left
  * NONFINITE with t_collapse = -2). */
 int adscl_step(adscl_ctx* ctx, int64_t max_steps, double t_end, int32_t snap_every,
                int32_t n_snap_slots, double* snaps, int mem);

@@ -40,9 +40,8 @@
 namespace adscl {
 namespace {
 
-// The per-instance stage scratch of the kernel that recomputes the stages, in
-// fields of [P][64 W] doubles: 16 for a step's stage record, two for the running
-// adjoint state while the stages are recomputed.
+// The per-instance stage scratch of the kernel that recomputes the stages: one step's
+// stage record, 16 fields of [P][64 W] doubles (four stages of Phi, Pi, e^-delta and w).
 constexpr int kFields = 16;
 
 // Sum of the wavefront totals r[0..W) over the wavefronts after this one
@@ -489,7 +488,7 @@ __global__ void __launch_bounds__(64 * W) adjoint_kernel(AdjointArgs a)
         load_v(uni(st + 3 * kStage));
     }
     for (int t = n_seg - 1; t >= 0; --t) {
-        // the stage inputs V_s of step t and their e^-delta and S: read from the
+        // the stage inputs V_s of step t and their e^-delta and w: read from the
         // record, or recomputed from U^t into the scratch
         if constexpr (!REC) {
             const ADSCL_GLOBAL double* u = gmem(a.seg[b]) + (size_t)t * 2 * (size_t)N;
@@ -512,7 +511,7 @@ __global__ void __launch_bounds__(64 * W) adjoint_kernel(AdjointArgs a)
 #pragma unroll 1
             for (int s = 0; s < 4; ++s) {
                 double r0[P], r1[P];
-                // stores V_s, e^-delta and S as stage s of the scratch's record
+                // stores V_s, e^-delta and w as stage s of the scratch's record
                 sg.template rhs<true>(false, false, cv0, cv1, r0, r1, uni(st), s);
                 if (s < 3) {
                     const double c_next = (s == 2) ? dt : 0.5 * dt;

@@ -17,10 +17,12 @@
 //       ghosts in LDS; each lane applies the centred D and the Kreiss-Oliger
 //       stencils to its points (Eqs. (2)-(3)), does the RK4 combination and
 //       publishes the next stage input.
-// Between the first and the last step of a segment nothing goes to HBM but
-// the coefficient-table reads (L2-resident); the segment ends at the call's
+// The coefficient tables sit in LDS for the whole launch, so between its first and its
+// last step nothing goes to memory but the adjoint's checkpoints and stage records,
+// where it asks for them.  A segment ends at the call's
 // last step or at the next snapshot step, where the finalize kernel solves the
-// constraints of the state for the outputs (A, delta, m).
+// constraints of the state for the outputs (A, delta, m); it may take several launches
+// (segment_end in internal.h).
 //
 // The stage machinery (LDS layout, parity ghosts, the two scans, fluxes)
 // lives in stage.h, shared with the adjoint kernel's forward recomputation.
