@@ -96,6 +96,7 @@ struct adscl_ctx {
     const double** d_wPhi = nullptr;
     std::map<int, NTables> tables;
     std::vector<LaunchClass> classes;
+    std::vector<hipStream_t> streams;  // the classes', in the order of their creation
     double* d_tmp = nullptr;    // staging for host inputs / outputs
     size_t tmp_bytes = 0;
     // adjoint working memory, kept for reuse by later calls
@@ -378,27 +379,35 @@ int buffer(adscl_ctx* c, const char* name, size_t bytes, void** out)
 }
 
 // One launch per selected class, the classes concurrently (one stream per class, forked
-// from and joined back into the context stream; class `here` on the context's own).
-// `launch(lc, stream)` enqueues the class's work.
+// from and joined back into the context stream).  `launch(lc, stream)` enqueues the class's
+// work.  `here`: that class on the context's own stream, and the others on the streams
+// created first, since of a process's few hardware queues the context's stream most likely
+// shares one with a stream created late (1024 instances of three grids in slices: 20.9 ms;
+// 25.0 where the two classes that run side by side share a queue).
 template <class F, class Sel>
 int run_classes(adscl_ctx* c, F&& launch, Sel&& selected, const LaunchClass* here = nullptr)
 {
     hipEvent_t fork = c->fork;
     if (fork) HIP_TRY(c, hipEventRecord(fork, c->stream));
-    auto stream_of = [&](const LaunchClass& lc) { return lc.stream && &lc != here ? lc.stream : c->stream; };
-    for (LaunchClass& lc : c->classes) {
+    std::vector<hipStream_t> on(c->classes.size(), c->stream);
+    size_t taken = 0;
+    for (size_t k = 0; k < on.size(); ++k) {
+        const LaunchClass& lc = c->classes[k];
+        if (lc.chunks > 0 || !selected(lc) || !lc.stream || &lc == here) continue;
+        on[k] = here ? c->streams[taken++] : lc.stream;
+    }
+    for (size_t k = 0; k < on.size(); ++k) {
+        LaunchClass& lc = c->classes[k];
         if (lc.chunks > 0 || !selected(lc)) continue;
-        const hipStream_t s = stream_of(lc);
-        if (s != c->stream) HIP_TRY(c, hipStreamWaitEvent(s, fork, 0));
-        HIP_TRY(c, launch(lc, s));
-        if (s != c->stream) HIP_TRY(c, hipEventRecord(lc.done, s));
+        if (on[k] != c->stream) HIP_TRY(c, hipStreamWaitEvent(on[k], fork, 0));
+        HIP_TRY(c, launch(lc, on[k]));
+        if (on[k] != c->stream) HIP_TRY(c, hipEventRecord(lc.done, on[k]));
     }
     // joined only now: a class whose stream shares the context's hardware queue waits for
     // none of the others (192 ragged instances of six classes 11.7 ms, 14.6 with each joined
     // at once)
-    for (LaunchClass& lc : c->classes)
-        if (lc.chunks == 0 && selected(lc) && stream_of(lc) != c->stream)
-            HIP_TRY(c, hipStreamWaitEvent(c->stream, lc.done, 0));
+    for (size_t k = 0; k < on.size(); ++k)
+        if (on[k] != c->stream) HIP_TRY(c, hipStreamWaitEvent(c->stream, c->classes[k].done, 0));
     return ADSCL_OK;
 }
 
@@ -483,8 +492,7 @@ int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const E
     // by side.
     // Measured, ms, against every class in one launch on a stream of its own: 1024
     // instances of 1025, 2049 and 4097 points, 512 steps, 26.7 -> 20.8; 250 + 324 + 349 of
-    // 4097, 2049 and 1025, 256 steps, 10.5 -> 8.8 (11.1 where the runtime gives the last two
-    // one hardware queue); 300 of 4097, 8.5 -> 5.3; 600 of 2049, 6.5 -> 5.0.
+    // 4097, 2049 and 1025, 256 steps, 10.5 -> 8.8; 300 of 4097, 8.5 -> 5.3; 600 of 2049, 6.5 -> 5.0.
     int n_slices = 1;
     // Only where few instances stop on the way, in calls of at most a light crossing,
     // t = pi/2, of the largest grid: a launch of a whole class hands the place of an
@@ -549,8 +557,7 @@ int run_evolve(adscl_ctx* c, const EvolveArgs& base, bool timing = true, const E
     };
     for (LaunchClass& lc : c->classes)
         if (alone(lc)) HIP_TRY(c, launch(lc, c->stream));
-    // Cut into slices, the largest of the others goes first, on the context's stream (1024
-    // instances of three grids, 512 steps: 20.9 ms; 22.6 where the smaller class got in first).
+    // Cut into slices, the largest of the others goes first, on the context's stream.
     const LaunchClass* first = nullptr;
     for (const LaunchClass& lc : c->classes)
         if (n_slices > 1 && !first && lc.chunks == 0 && !alone(lc)) first = &lc;
@@ -1249,6 +1256,7 @@ int adscl_create(const adscl_config* cfg, void* hip_stream, adscl_ctx** out)
         // first.
         if (lc.chunks == 0 && c->classes.size() > 1) {
             TRY_C(hipStreamCreateWithFlags(&lc.stream, hipStreamNonBlocking));
+            c->streams.push_back(lc.stream);
             TRY_C(hipEventCreateWithFlags(&lc.done, hipEventDisableTiming));
         }
         if (c->flags & ADSCL_TIME_KERNELS) {

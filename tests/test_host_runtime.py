@@ -295,3 +295,37 @@ def test_creating_a_context_takes_few_allocations_and_copies(L):
     c.step(10)
     c.close()
     assert L.fake_in_use() == held
+
+
+def test_the_classes_beside_one_another_in_a_cut_call(L):
+    """The largest of them on the context's stream, the others on the streams created first,
+    each on its own; the class that fills the device before them, on the context's stream."""
+    L.fake_reset(TOTAL, TOTAL, 4, 1)
+    c = Ctx(L, [4097] * 5 + [2049] * 3 + [1025] * 1 + [513])
+    c.init()
+    L.fake_reset(TOTAL, TOTAL, 4, 1)
+    c.step(512, 1e9)
+    assert np.all(c.status()[0] == 512)
+    log = [l.split() for l in L.fake_log().decode().split("\n") if l]
+    main = next(l[1] for l in log if l[0] == "record")
+    on = {}
+    for l in log:
+        if l[0] == "evolve":
+            on.setdefault(l[2] + l[3], set()).add(l[1])
+    assert on["P8W8"] == on["P8W4"] == {main}
+    small = [on["P4W4"], on["P4W2"]]
+    assert all(len(s) == 1 for s in small) and len(set.union(*small)) == 2 and main not in set.union(*small)
+    made = sorted(int(x) for x in {l[1] for l in log if l[0] == "wait" and l[1] != main})
+    assert sorted(int(x) for s in small for x in s) == made
+    c.close()
+    # the streams are the two created first, whichever class appeared first
+    L.fake_reset(TOTAL, TOTAL, 4, 1)
+    c = Ctx(L, [1025] + [2049] * 3 + [4097] * 5 + [513])
+    c.init()
+    c.step(20)  # not cut: every class on its own stream
+    own = {l.split()[2] + l.split()[3]: int(l.split()[1]) for l in c.launches()}
+    L.fake_reset(TOTAL, TOTAL, 4, 1)
+    c.step(512, 1e9)
+    used = {int(l.split()[1]) for l in c.launches()} & set(own.values())
+    assert used == set(sorted(own.values())[:2])
+    c.close()
