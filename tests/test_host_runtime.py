@@ -329,3 +329,25 @@ def test_the_classes_beside_one_another_in_a_cut_call(L):
     used = {int(l.split()[1]) for l in c.launches()} & set(own.values())
     assert used == set(sorted(own.values())[:2])
     c.close()
+
+
+def test_the_adjoints_largest_class_runs_on_the_contexts_stream(L, monkeypatch):
+    """And the others on the streams created first, in the forward run and the reverse
+    sweep, with and without stage records."""
+    monkeypatch.setenv("ADSCL_ADJOINT_SEGMENTS", "1")
+    for env in ("", "1"):
+        monkeypatch.setenv("ADSCL_ADJOINT_RECOMPUTE", env)
+        L.fake_reset(TOTAL, TOTAL, 4, 1)
+        c = Ctx(L, [1025, 257, 4097], n_modes=1)
+        c.limit = TOTAL
+        rc, _, n = adjoint(c, 30, 0.02)
+        assert rc == 0 and n > 1
+        log = [l.split() for l in L.fake_log().decode().split("\n") if l]
+        main = next(l[1] for l in log if l[0] == "record")
+        on = {}
+        for l in log:
+            if l[0] == "evolve":
+                on.setdefault(l[2] + l[3], set()).add(l[1])
+        assert on["P8W8"] == {main} and all(len(s) == 1 for s in on.values()) and len(set.union(*on.values())) == 3
+        assert {l[1] for l in log if l[0] == "reverse"} == set.union(*on.values())
+        c.close()
