@@ -112,8 +112,7 @@ def adjoint_rate(adscl, T, iters=2, warmup=1):
     """Gradients per second of the batched descent loop: the 256-instance
     mode-data draw (N in {2049, 4097}, 32 modes, drift of 16 modes,
     checkpoints every 512 steps) over a window of T time units; each iteration
-    is one forward evolution and one reverse sweep of every instance, replayed
-    from a captured graph."""
+    is one forward evolution and one reverse sweep of every instance."""
     import torch
     from paper_1706_07413_amd import inputs as I
     cfg = I.config4()

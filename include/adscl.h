@@ -228,7 +228,8 @@ int adscl_adjoint(adscl_ctx* ctx, const double* eps, const double* c, int32_t Jc
  * c [n_inst x Jc] is read and overwritten with the final coefficients; L_hist
  * [iters x n_inst]; active [n_inst] (int32).  Other arguments as adscl_adjoint;
  * iters >= 1, step0 > 0.  One iteration is captured into a HIP graph once and
- * replayed `iters` times; ADSCL_DESCEND_EAGER enqueues every iteration
+ * replayed `iters` times where all instances share one kernel configuration; where
+ * not, and with ADSCL_DESCEND_EAGER, every iteration is enqueued
  * directly instead (same results, bit for bit). */
 enum { ADSCL_DESCEND_EAGER = 1 };
 int adscl_descend(adscl_ctx* ctx, const double* eps, double* c, int32_t Jc, int32_t J, double T,

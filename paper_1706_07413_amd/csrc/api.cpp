@@ -1706,9 +1706,17 @@ int adscl_descend(adscl_ctx* c, const double* eps, double* coef, int32_t Jc, int
                                     (double*)hist, c->stream));
         return ADSCL_OK;
     };
-    if (flags & ADSCL_DESCEND_EAGER) {
+    // Where the classes run on several streams the graph would have branches, which the
+    // runtime replays on streams that it makes and unmakes with the graph.  A process that
+    // made and unmade many graphs of three branches once ended in a host segmentation fault
+    // whose cause is not known, so such contexts enqueue their iterations one by one: the
+    // same time (256 instances of two grids, two iterations: 114 ms; 111 to 116 replayed),
+    // since the host takes less for the launches of an iteration than the device.
+    const bool branches = c->classes.size() > 1;
+    if ((flags & ADSCL_DESCEND_EAGER) || branches) {
         for (int i = 0; i < iters; ++i)
-            if ((rc = one_iteration(true))) return rc;
+            if ((rc = one_iteration((flags & ADSCL_DESCEND_EAGER) != 0))) return rc;
+        if (!(flags & ADSCL_DESCEND_EAGER)) HIP_TRY(c, hipStreamSynchronize(c->stream));  // as after the replays
     } else {
         // one iteration captured once, replayed `iters` times
         hipGraph_t graph = nullptr;

@@ -35,6 +35,7 @@ def L(tmp_path_factory):
                             ("adscl_step", _i32, [_vp, _i64, _d, _i32, _i32, _vp, _i32]),
                             ("adscl_status", _i32, [_vp] * 6), ("adscl_last_error", ctypes.c_char_p, [_vp]),
                             ("adscl_adjoint", _i32, [_vp, _vp, _vp, _i32, _i32, _d, _i32, _vp, _vp, _vp, _i32]),
+                            ("adscl_descend", _i32, [_vp, _vp, _vp, _i32, _i32, _d, _i32, _i32, _d, _i32, _vp, _vp, _i32]),
                             ("fake_reset", None, [_i64, _i64, _i32, _i32]), ("fake_log", ctypes.c_char_p, []),
                             ("fake_in_use", _i64, []), ("fake_setup", _i64, []), ("fake_peak", _i64, []), ("fake_refused", _i64, [])):
         getattr(lib, name).restype, getattr(lib, name).argtypes = res, args
@@ -328,6 +329,26 @@ def test_the_classes_beside_one_another_in_a_cut_call(L):
     c.step(512, 1e9)
     used = {int(l.split()[1]) for l in c.launches()} & set(own.values())
     assert used == set(sorted(own.values())[:2])
+    c.close()
+
+
+@pytest.mark.parametrize("Ns,graph", [([65] * 3, True), ([257, 257], True), ([65, 1025], False), ([1025, 2049, 4097], False),
+                                      ([257, 259], False)])
+def test_descent_iterations_are_captured_only_without_branches(L, Ns, graph):
+    """One class: an iteration captured once and replayed; several: every one enqueued, in
+    the same order, with no capture."""
+    L.fake_reset(TOTAL, TOTAL, 4, 1)
+    c = Ctx(L, Ns, n_modes=1)
+    n, iters = len(Ns), 3
+    eps, coef, hist, act = np.ones(n), np.ones((n, 1)), np.zeros((iters, n)), np.zeros(n, np.int32)
+    for eager in (0, 1):
+        L.fake_reset(TOTAL, TOTAL, 4, 1)
+        assert L.adscl_descend(c.h, eps.ctypes.data, coef.ctypes.data, 1, 1, 0.02, 8, iters, 0.05, eager, hist.ctypes.data,
+                               act.ctypes.data, 0) == 0
+        log = L.fake_log().decode().split("\n")
+        once = graph and not eager
+        assert log.count("capture") == once and log.count("replay") == (iters if once else 0)
+        assert len([l for l in log if l.startswith("segment 0 ")]) == (1 if once else iters)
     c.close()
 
 
